@@ -52,8 +52,8 @@ METRIC = "effective HBM GB/s (and % of peak) for tree-reduce+SGD step; µs per s
 CSRC = os.path.join(ROOT, "paper_1511_00175_amd", "csrc")
 
 
-KERNEL_SOURCES = ("fc_device.h", "fc_internal.h", "fc_shape.h", "fc_reduce_f32.hip", "fc_reduce_f16.hip",
-                  "fc_update.hip")
+KERNEL_SOURCES = ("fc_device.h", "fc_split.h", "fc_internal.h", "fc_shape.h", "fc_reduce_f32.hip",
+                  "fc_reduce_f16.hip", "fc_update.hip")
 
 
 def _code_tokens(text):

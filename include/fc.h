@@ -125,11 +125,18 @@ typedef struct fc_plan fc_plan;
  *   MI355X (VGG-19 K=16 fp32, 8 rounds: 1802-1805 us per step vs 1763-1764
  *   us with one launch per round): within one launch the blocks drift apart,
  *   so one round's writes meet the next round's replica reads.
- * AUTO (no launch-shape field given): FUSED for a step of less than 64 MiB
- *   (n_elems * (K * bytes per element + 16)); otherwise RESIDENT when one
- *   round holds the plan or a parameter's replicas take at least 48 bytes
- *   (K * bytes per element), else FUSED.  With a launch-shape field: TWO_PASS when they take more than
- *   256 bytes, else FUSED. */
+ * AUTO (no launch-shape field given): a plan of more than 16 replicas and at
+ *   most 6 tiles of 256 elements per compute unit (5 for fp16 replicas in
+ *   linear order; with K <= 32 fewer than 2) runs FUSED, or TWO_PASS
+ *   with both passes in one launch when a parameter's replicas take more than
+ *   256 bytes (K * bytes per element): its waves share the replicas of a
+ *   tile, and the sum goes from the reduction to the update through LDS, so
+ *   that every call is one launch and the plan owns no raw-sum scratch.  Any
+ *   other step of less than 64 MiB (n_elems * (K * bytes per element + 16))
+ *   runs FUSED; a larger one RESIDENT when one round holds the plan or a
+ *   parameter's replicas take at least 48 bytes, else FUSED.  With a
+ *   launch-shape field: TWO_PASS when they take more than 256 bytes, else
+ *   FUSED. */
 typedef enum {
     FC_SCHED_AUTO = 0,
     FC_SCHED_FUSED = 1,
@@ -143,7 +150,9 @@ typedef enum {
  * schedule, the replica type, K and the plan's size (measured on MI355X):
  * RESIDENT -> 64-lane tiles of (2 vectors, batches of 4 replicas) for fp32
  * replicas with K <= 16, else (1 vector, batches of 16); vecs_per_thread and
- * kchunk may name either; otherwise fp16 -> (4 vectors, 4 replicas, 256
+ * kchunk may name either; a step whose waves share the replicas of a tile
+ * (see AUTO) -> tiles of 64 lanes x 1 or 2 elements, up to 16 waves per block,
+ * batches of 16; otherwise fp16 -> (4 vectors, 4 replicas, 256
  * threads); fp32 with K <= 4 -> (1, 8, 256); fp32 with 16 < K <= 64 ->
  * (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the
  * streaming (nt) hint. */
@@ -164,7 +173,7 @@ typedef struct {
  * then does nothing).  1 <= K <= 1024.  Offsets must be multiples of 4
  * elements (16 bytes of fp32, 8 bytes of fp16).  Allocates the plan's device
  * tables on the current device with hipMalloc (FC_EHIP on failure); when
- * fc_step's schedule resolves to TWO_PASS the plan also owns a raw-sum
+ * fc_step runs TWO_PASS in two launches the plan also owns a raw-sum
  * scratch buffer of 4 bytes per element of the segment extent.
  *   gdt   : an fc_dtype value, order: an fc_order value (plain ints, so that
  *           any value a caller passes is defined; others are FC_EINVAL)
@@ -307,7 +316,7 @@ typedef struct {
     int ntiles;          /* blocks of work in one launch */
     int grid;            /* blocks launched (RESIDENT: its persistent grid) */
     int block_threads;   /* threads per block of the reduce or step launch */
-    int vecs_per_thread;
+    int vecs_per_thread; /* (1 where a lane's share is less than one vector) */
     int kchunk;
     int schedule;        /* resolved fc_schedule of fc_step: FUSED, TWO_PASS, RESIDENT or
                             RESIDENT_ONE_LAUNCH (only when asked for) */

@@ -160,23 +160,28 @@ int order_after_last(fc_plan* p, hipStream_t s, bool& note) {
 // (order_after_last ran first).  Not while `s` is being captured into a
 // graph: the graph would record a copy from the plan's host buffer, which
 // later calls overwrite, so a capture may only hold calls that keep the
-// tables.  `host` has K entries from plan creation on, so assigning K new
-// ones allocates nothing.
+// tables.  `host` has its size from plan creation on (nothing is allocated
+// here): K entries and SPLIT_PAD more, which repeat the last one for kernels
+// that read whole batches of pointers.
 template <typename P>
 int update_table(fc_plan* p, std::vector<P>& host, bool& valid, P* dev, const P* want, hipStream_t s) {
     const size_t K = static_cast<size_t>(p->K);
-    if (valid && std::equal(host.begin(), host.end(), want)) return FC_OK;
+    if (valid && std::equal(want, want + K, host.begin())) return FC_OK;
     const int rc = capture_check(s);
     if (rc) return rc;
-    host.assign(want, want + K);
+    std::copy(want, want + K, host.begin());
+    std::fill(host.begin() + K, host.end(), want[K - 1]);
     valid = false;
-    if (hipMemcpyAsync(dev, host.data(), K * sizeof(P), hipMemcpyHostToDevice, s) != hipSuccess)
+    if (hipMemcpyAsync(dev, host.data(), host.size() * sizeof(P), hipMemcpyHostToDevice, s) != hipSuccess)
         return FC_EHIP;
     valid = true;
     return FC_OK;
 }
 
 hipError_t launch_reduce(const fc::Shape& sh, int mode, int grid, const fc::ReduceArgs& a, hipStream_t s) {
+    if (sh.lane)
+        return sh.dtype == FC_F16 ? fc::launch_split_f16(sh, mode, grid, a, s)
+                                  : fc::launch_split_f32(sh, mode, grid, a, s);
     return sh.dtype == FC_F16 ? fc::launch_reduce_f16(sh, mode, grid, a, s) : fc::launch_reduce_f32(sh, mode, grid, a, s);
 }
 
@@ -401,9 +406,16 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
         res_c = opts->kchunk;
     }
     const uint64_t tile_vecs_r = 64 * static_cast<uint64_t>(res_u);
-    uint64_t res_tiles = 0;
-    for (int j = 0; j < nseg; ++j)
-        res_tiles += (segs[j].length / vec + tile_vecs_r - 1) / tile_vecs_r + (segs[j].length % vec ? 1 : 0);
+    auto tiles_of = [&](uint64_t vecs) {  // tiles of at most `vecs` lane-vectors (saturating)
+        uint64_t n = 0;
+        for (int j = 0; j < nseg; ++j) {
+            const uint64_t nvec = segs[j].length / vec;
+            const uint64_t t = nvec / vecs + (nvec % vecs ? 1 : 0) + (segs[j].length % vec ? 1 : 0);
+            n = t > UINT64_MAX - n ? UINT64_MAX : n + t;
+        }
+        return n;
+    };
+    const uint64_t res_tiles = tiles_of(tile_vecs_r);
     const uint64_t slot_bytes = fc::RESIDENT_SLOT * sizeof(float) * res_u;
     const uint64_t cap_lds = std::max<uint64_t>(1, static_cast<uint64_t>(std::max(lds_cu, 0)) / slot_bytes);
     int res_grid = std::max(1, cus);
@@ -433,10 +445,14 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     // algorithmic bytes of one step (saturating)
     const uint64_t per_elem = static_cast<uint64_t>(K) * (gdt == FC_F16 ? 2 : 4) + 16;
     const uint64_t step_bytes = n_elems > UINT64_MAX / per_elem ? UINT64_MAX : n_elems * per_elem;
-    const bool resident =
-        res_req ||
-        (sched_req == FC_SCHED_AUTO && !shape_given &&
-         fc::default_resident(K, gdt == FC_F16 ? 2 : 4, static_cast<int64_t>(res_rounds), step_bytes));
+    const bool choose = sched_req == FC_SCHED_AUTO && !shape_given;
+    // tiles of 256, 128 and 64 elements: is the plan too short to fill the
+    // chip with one wave per tile?
+    const bool split = choose && fc::default_split(gdt, order == FC_ORDER_TREE, K, std::max(1, cus), tiles_of(64),
+                                                   tiles_of(32), tiles_of(16), sh);
+    const bool resident = res_req || (choose && !split &&
+                                      fc::default_resident(K, gdt == FC_F16 ? 2 : 4, static_cast<int64_t>(res_rounds),
+                                                           step_bytes));
     if (resident) {
         sh.block = 64;
         sh.vecs = res_u;
@@ -455,7 +471,7 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     p->extent = end;
     sh.dtype = gdt;
     sh.tree = order == FC_ORDER_TREE;
-    sh.maxd = bit_length(K / sh.kchunk);
+    sh.maxd = split ? 1 : bit_length(K / sh.kchunk);  // the split kernel's stack is its own
     if (sh.maxd > fc::MAXD_MAX) {
         delete p;
         return FC_EINVAL;
@@ -469,7 +485,8 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     try {
         p->segs.assign(segs, segs + nseg);
         mults.resize(2 * static_cast<size_t>(std::max(nseg, 1)));
-        const uint64_t tile_vecs = static_cast<uint64_t>(sh.block) * sh.vecs;
+        const uint64_t tile_vecs = split ? 16 * static_cast<uint64_t>(sh.lane)  // 64 lanes of sh.lane elements
+                                         : static_cast<uint64_t>(sh.block) * sh.vecs;
         for (int j = 0; j < nseg; ++j) {
             const fc_segment& s = segs[j];
             mults[2 * j] = s.lr_mult;
@@ -491,8 +508,8 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
                 tiles.push_back(t);
             }
         }
-        p->h_grads.assign(K, nullptr);
-        p->h_dst.assign(K, nullptr);
+        p->h_grads.assign(K + fc::SPLIT_PAD, nullptr);
+        p->h_dst.assign(K + fc::SPLIT_PAD, nullptr);
     } catch (const std::bad_alloc&) {
         delete p;
         return FC_ENOMEM;
@@ -531,9 +548,9 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     bool ok = hipEventCreateWithFlags(&p->order_event, hipEventDisableTiming) == hipSuccess &&
               hipMalloc(&p->d_tiles, std::max<size_t>(tiles.size(), 1) * sizeof(Tile)) == hipSuccess &&
               hipMalloc(&p->d_mults, mults.size() * sizeof(float)) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void**>(&p->d_grads), K * sizeof(void*)) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void**>(&p->d_dst), K * sizeof(float*)) == hipSuccess;
-    if (ok && p->schedule == FC_SCHED_TWO_PASS && p->extent > 0)
+              hipMalloc(reinterpret_cast<void**>(&p->d_grads), p->h_grads.size() * sizeof(void*)) == hipSuccess &&
+              hipMalloc(reinterpret_cast<void**>(&p->d_dst), p->h_dst.size() * sizeof(float*)) == hipSuccess;
+    if (ok && p->schedule == FC_SCHED_TWO_PASS && !split && p->extent > 0)
         ok = hipMalloc(&p->d_sum, static_cast<size_t>(p->extent) * sizeof(float)) == hipSuccess;
     if (ok && resident) {
         const size_t clock_bytes = static_cast<size_t>(res_grid) * fc::RESIDENT_CLOCK_WORDS * sizeof(unsigned long long);
@@ -894,8 +911,9 @@ static int fc_step_body(fc_plan* p, const void* const* grads, float* w, float* v
     if (rc) return rc;
     rc = update_step_tables(p, grads, bcast_dst, s);
     const float c = 1.0f / static_cast<float>(batch);
-    if (rc == FC_OK && p->schedule == FC_SCHED_TWO_PASS) {
-        // pass 1: raw sum into `out` (or the plan's scratch); pass 2: update (+ broadcast)
+    if (rc == FC_OK && p->schedule == FC_SCHED_TWO_PASS && !p->shape.lane) {
+        // pass 1: raw sum into `out` (or the plan's scratch); pass 2: update
+        // (+ broadcast).  On a split plan one launch does both passes' work.
         rc = two_pass(p, p->shape, out ? out : p->d_sum, w, v, lr, mu, wd, c, bcast_dst != nullptr, s, true);
     } else if (rc == FC_OK) {
         fc::ReduceArgs a{};
@@ -938,7 +956,7 @@ static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, 
     // so its reduce pass loads batches of 8 (the association does not depend
     // on the batch)
     fc::Shape sh = p->shape;
-    if (!fc::compiled_pair(sh.vecs, sh.kchunk)) {
+    if (!sh.lane && !fc::compiled_pair(sh.vecs, sh.kchunk)) {
         sh.kchunk = 8;
         sh.maxd = bit_length(p->K / sh.kchunk);
     }

@@ -31,6 +31,8 @@
 // Kernels (all share the loads, the register stack and the epilogue, so they
 // give the same bits):
 //   reduce_kernel   one tile per block; reduce-only, or the fused step
+//   split_kernel    the same for short steps, the replicas of a tile shared by
+//                   the waves of a block (fc_split.h)
 //   resident_kernel one persistent block per CU: reduce a range of tiles into
 //                   LDS and registers (pure reads), then finish it from there:
 //                   w' stored, v' parked and stored after a barrier (or, with
@@ -862,7 +864,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(SgdArgs a) {
         const int j = static_cast<int>(tile.seg & SEG_MASK);
         const float lr_j = a.lr * ldc(a.mults, 2 * j);
         const float wd_j = a.wd * ldc(a.mults, 2 * j + 1);
-        if (!(tile.seg & TAIL_BIT)) sgd_body<V, U>(a, tile.start, tile.count, lr_j, wd_j);
+        if (!(tile.seg & TAIL_BIT)) sgd_body<V, U>(a, tile.start, tile.count * (4 / V), lr_j, wd_j);
         else sgd_body<1, 1>(a, tile.start, tile.count, lr_j, wd_j);
     }
 }
@@ -888,7 +890,7 @@ template <int V, int U>
 __global__ __launch_bounds__(256) void bcast_kernel(BcastArgs a) {
     for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         const Tile tile = ld_tile(a.tiles, t);
-        if (!(tile.seg & TAIL_BIT)) bcast_body<V, U>(a, tile.start, tile.count);
+        if (!(tile.seg & TAIL_BIT)) bcast_body<V, U>(a, tile.start, tile.count * (4 / V));
         else bcast_body<1, 1>(a, tile.start, tile.count);
     }
 }

@@ -34,6 +34,11 @@ struct Shape {
     int kchunk;       // replicas loaded per batch (2, 4, 8 or 16; see the pairs compiled)
     int maxd;         // depth of the pending-subtree stack (>= bit length of K / kchunk)
     int rtiles;       // resident kernel: tiles per wave whose raw sums stay in registers
+    // split kernel (0 lanes: not used): tiles of 64 lanes x `lane` elements,
+    // `waves` waves per tile, wave q on the replicas [q run, (q + 1) run)
+    int lane;
+    int waves;
+    int run;
 };
 
 struct ReduceArgs {
@@ -68,6 +73,8 @@ struct ResidentArgs {
 constexpr int RESIDENT_CLOCK_WORDS = 4;
 constexpr int RESIDENT_SLOT = 256;  // floats per tile of 64 lanes x one 4-element vector
 constexpr int RESIDENT_WAVES = 16;
+constexpr int SPLIT_WAVES = 16;     // most waves that share a tile (split_kernel)
+constexpr int SPLIT_PAD = 16;       // readable entries of a replica table past the last replica
 
 struct SgdArgs {
     const Tile* tiles;
@@ -97,6 +104,8 @@ constexpr int MAXD_MAX = 10;
 
 hipError_t launch_reduce_f32(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_reduce_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
+hipError_t launch_split_f32(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
+hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s);
 hipError_t launch_bcast(const Shape& sh, int grid, const BcastArgs& a, hipStream_t s);
 hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, const BcastArgs& a, hipStream_t s);

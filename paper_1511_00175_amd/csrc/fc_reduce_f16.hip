@@ -1,10 +1,15 @@
 // Reduce and fused-step kernels for fp16 replicas.
 #include "fc_device.h"
+#include "fc_split.h"
 
 namespace fc {
 
 hipError_t launch_reduce_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s) {
     return launch_reduce_dt<FC_F16>(sh, mode, grid, a, s);
+}
+
+hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s) {
+    return launch_split_dt<FC_F16>(sh, mode, grid, a, s);
 }
 
 hipError_t launch_resident_f16(const Shape& sh, int mode, int grid, size_t lds, const ResidentArgs& a,

@@ -4,6 +4,7 @@
 // device code.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 
 #include "fc.h"
@@ -82,6 +83,59 @@ inline bool resident_fits_k(int u, int c, int K) { return u == 1 || K / c < 128;
 inline int resident_rtiles(int gdt, int u, int c, int maxd) {
     if (gdt == FC_F16 && u == 1 && c == 16 && maxd <= 5) return 4;
     return gdt == FC_F32 && u == 2 && c == 4 && maxd <= 3 ? 4 : 0;
+}
+
+// The split kernel (a tile is a block's work, its waves share the replicas)
+// for plans of at most 6 tiles of 256 elements per compute unit (5 for fp16 in
+// linear order, where the one wave that adds has the most to do): one wave per
+// tile, or a resident block's share of them, leaves most of the chip idle.
+// With K <= 16 one wave asks for all replicas in one batch, and with K <= 32
+// it does so in two, which two tiles per unit hide: those stay with one wave
+// per tile.  Measured on MI355X (us per step in a HIP graph, before / now /
+// the bytes at 7 TB/s): fp32 4096 x K=1000 59 / 6.5 / 2.4, 16384 x K=128 10.7
+// / 2.8 / 1.2, 2^16 x K=64 39 / 5.0 / 2.5, 2^16 x K=256 20.3 / 12.0 / 9.7,
+// 2^18 x K=128 24.9 / 23.8 / 19.8; fp16 16384 x K=1000 428 / 8.3 / 4.7, 2^16 x
+// K=128 44 / 4.8 / 2.5, 2^18 x K=64 22 / 8.5 / 5.4; linear order fp32 8274 x
+// K=1000 52 / 12.6 / 4.7, fp16 2^16 x K=128 58 / 5.7 / 2.5.  From 6 tiles per
+// unit on the older kernels are as fast or faster (400000 x K=64, split /
+// one wave per tile: fp32 19.6 / 19.4, fp16 11.4 / 10.9, linear 12.6 / 10.7;
+// fp16 linear 362028 x K=100, split / resident 17.3 / 15.5).
+//
+// Tiles of 128 elements where that leaves two per unit (fp16: one, its rows
+// are half as long), else of 64.  Tree: runs of 16 replicas, one batch, while
+// that makes at most 32 waves' worth of 64-element tiles per unit, else of 32
+// (2^18 x K=256 with runs of 32 / 64: 42.9 / 51.2; 2^16 x K=256 with 16 / 32:
+// 13.0 / 12.0), and of 64 where that takes more than 8 waves (2^17 x K=400
+// with 32 / 64: 36.5 / 34.0, K=512 43.5 / 42.2) or, in a narrower grid, 16.  Linear: as many waves as keep 4 KiB
+// of each replica's row per unit in the block's batches, to the nearest power
+// of two: more only wait for the one that adds (fp16 200000 x K=128 with 2 / 4
+// waves 10.9 / 12.9, 2^16 x K=1000 with 4 / 8 24.6 / 22.2); the batches of all
+// waves fit 64 KiB of LDS.
+inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, uint64_t tiles256, uint64_t tiles128,
+                          uint64_t tiles64, fc::Shape& sh) {
+    const uint64_t cu = static_cast<uint64_t>(cus);
+    const uint64_t most = !tree && gdt == FC_F16 ? 5 : 6;
+    if (K <= 16 || tiles256 > most * cu || (K <= 32 && tiles256 >= 2 * cu)) return false;
+    sh.lane = tiles128 >= (gdt == FC_F16 ? cu : 2 * cu) ? 2 : 1;
+    const uint64_t width = sh.lane == 2 ? 2 * tiles128 : tiles64;  // the grid's width in 64-element tiles
+    sh.run = 16;
+    const int batches = (K + 15) / 16;
+    if (tree) {
+        const bool many = width * static_cast<uint64_t>(batches) > 32 * cu;
+        if (many) sh.run = 32;
+        while (sh.run < 64 && (K + sh.run - 1) / sh.run > (many ? SPLIT_WAVES / 2 : SPLIT_WAVES)) sh.run *= 2;
+        sh.waves = (K + sh.run - 1) / sh.run;
+    } else {
+        const uint64_t budget = (gdt == FC_F16 ? 32 : 16) * cu;
+        sh.waves = SPLIT_WAVES / sh.lane;
+        // halve while the next smaller power of two is nearer (ratio above sqrt 2)
+        while (sh.waves > sh.lane && 100 * width * static_cast<uint64_t>(sh.waves) > 141 * budget) sh.waves /= 2;
+        sh.waves = std::min(sh.waves, std::max(batches, sh.lane));
+    }
+    sh.block = 64 * sh.waves;
+    sh.vecs = 1;
+    sh.kchunk = 16;
+    return true;
 }
 
 inline bool compiled_pair(int u, int c) {

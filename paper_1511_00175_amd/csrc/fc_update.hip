@@ -33,6 +33,14 @@ hipError_t noalloc_scratch(int device, float** ptr) {
 }
 
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s) {
+    if (sh.lane) {  // tiles of 64 lanes x sh.lane elements
+        auto narrow = [&](auto v) {
+            hipLaunchKernelGGL((sgd_kernel<v.value, 1>), dim3(grid), dim3(64), 0, s, a);
+            return hipGetLastError();
+        };
+        if (sh.lane == 4) return narrow(I<4>{});
+        return pick<1, 2>(sh.lane, narrow);
+    }
     auto go = [&](auto u) {
         hipLaunchKernelGGL((sgd_kernel<4, u.value>), dim3(grid), dim3(sh.block), 0, s, a);
         return hipGetLastError();
@@ -42,6 +50,14 @@ hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s
 }
 
 hipError_t launch_bcast(const Shape& sh, int grid, const BcastArgs& a, hipStream_t s) {
+    if (sh.lane) {  // tiles of 64 lanes x sh.lane elements
+        auto narrow = [&](auto v) {
+            hipLaunchKernelGGL((bcast_kernel<v.value, 1>), dim3(grid), dim3(64), 0, s, a);
+            return hipGetLastError();
+        };
+        if (sh.lane == 4) return narrow(I<4>{});
+        return pick<1, 2>(sh.lane, narrow);
+    }
     auto go = [&](auto u) {
         hipLaunchKernelGGL((bcast_kernel<4, u.value>), dim3(grid), dim3(sh.block), 0, s, a);
         return hipGetLastError();
