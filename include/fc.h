@@ -152,7 +152,11 @@ typedef enum {
  * replicas with K <= 16, else (1 vector, batches of 16); vecs_per_thread and
  * kchunk may name either; a step whose waves share the replicas of a tile
  * (see AUTO) -> tiles of 64 lanes x 1 or 2 elements, up to 16 waves per block,
- * batches of 16; otherwise fp16 -> (4 vectors, 4 replicas, 256
+ * batches of 16; any other
+ * step of less than 64 MiB -> (1, 8, 256) for fp32 with K <= 8 or with K >= 12 and
+ * at least 1024 tiles of 256 elements, (4, 4, 256) for fp16 with K <= 4 and at least
+ * 4096 such tiles, else (1, 16, 64); otherwise (also with an explicit schedule
+ * or shape field) fp16 -> (4 vectors, 4 replicas, 256
  * threads); fp32 with K <= 4 -> (1, 8, 256); fp32 with 16 < K <= 64 ->
  * (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the
  * streaming (nt) hint. */

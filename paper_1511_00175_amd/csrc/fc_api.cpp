@@ -453,6 +453,8 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     const bool resident = res_req || (choose && !split &&
                                       fc::default_resident(K, gdt == FC_F16 ? 2 : 4, static_cast<int64_t>(res_rounds),
                                                            step_bytes));
+    if (choose && !split && !resident && step_bytes < fc::RESIDENT_MIN_BYTES)
+        fc::short_shape(gdt, K, tiles_of(64), sh);
     if (resident) {
         sh.block = 64;
         sh.vecs = res_u;

@@ -85,6 +85,29 @@ inline int resident_rtiles(int gdt, int u, int c, int maxd) {
     return gdt == FC_F32 && u == 2 && c == 4 && maxd <= 3 ? 4 : 0;
 }
 
+// Default shape of a step of less than RESIDENT_MIN_BYTES that one wave per
+// tile serves (default_split says no): blocks of 256 threads and batches of 8
+// for fp32 with few replicas or (unless a second batch would be nearly empty)
+// at least 1024 tiles of 256 elements, else one wave per block and batches of
+// 16; fp16 with K <= 4 and at least 2^20
+// elements keeps the 4-vector shape.  Measured on MI355X (us per step in a HIP
+// graph, (1, 8, 256) vs (1, 16, 64)): fp32 2^18 x K=8 3.6 vs 4.1, 500000 x
+// K=16 7.9 vs 8.4, 2^20 x K=8 10.1 vs 10.5, 2^17 x K=16 4.5 vs 3.7, 347457 x
+// K=9 5.2 vs 4.7; fp16
+// 2^20 x K=7 11.8 vs 7.3, K=12 12.4 vs 9.1, 2^18 x K=16 4.3 vs 4.1.  The
+// 4-vector shapes of default_shape leave most of the chip idle here: fp32
+// 2^18 x K=32 19.3 vs 7.7, fp16 2^18 x K=16 8.3 vs 4.1, 2^20 x K=16 11.4 vs
+// 10.0; 2^20 x K=4 5.9 vs 6.3.
+inline void short_shape(fc_dtype gdt, int K, uint64_t tiles256, fc::Shape& sh) {
+    if (gdt == FC_F16 && K <= 4 && tiles256 >= 4096) {
+        sh.vecs = 4; sh.kchunk = 4; sh.block = 256;
+    } else if (gdt == FC_F32 && (K <= 8 || (K >= 12 && tiles256 >= 1024))) {
+        sh.vecs = 1; sh.kchunk = 8; sh.block = 256;
+    } else {
+        sh.vecs = 1; sh.kchunk = 16; sh.block = 64;
+    }
+}
+
 // The split kernel (a tile is a block's work, its waves share the replicas)
 // for plans of at most 6 tiles of 256 elements per compute unit (5 for fp16 in
 // linear order, where the one wave that adds has the most to do): one wave per
