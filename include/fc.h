@@ -238,22 +238,22 @@ int fc_step(fc_plan* plan, const void* const* grads, float* w, float* v, float l
 
 /* For callers that cannot allocate device memory -- code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation: fc_step in
- * the two-pass schedule (a reduce pass into a raw-sum buffer, then the update
- * pass, which also stores the broadcast copies), whatever the plan's own
- * schedule, with the raw sum between the passes held in a fixed device array
- * of FC_NOALLOC_MAX_ELEMS floats (64 MiB) that the library reserves on each
- * GPU it runs on and keeps until the process ends.  Arguments, validation
- * and result bits are fc_step's.  When `out` is given it holds the raw sum
- * between the passes and the array is not used; otherwise the plan's extent
- * (one past its last segment element) must be at most FC_NOALLOC_MAX_ELEMS
- * (FC_ESIZE).  The current device must be the plan's (FC_EINVAL).  The call
- * allocates no device or host memory and records no per-kernel timing; like
- * every call it replaces a pointer table only when the pointers change.
- * Every call on one GPU uses that GPU's one array: calls that may run at the
- * same time on one GPU (other plans, other streams or threads) race on it;
- * calls on one plan are ordered (see the conventions above).  The array
- * needs no clearing: the reduce pass writes every segment element before the
- * update pass reads it. */
+ * the plan's own schedule, where a TWO_PASS plan of two launches holds the
+ * raw sum between them in a fixed device array of FC_NOALLOC_MAX_ELEMS floats
+ * (64 MiB) that the library reserves on each GPU it runs on and keeps until
+ * the process ends (the other schedules keep the sum on chip).  Arguments,
+ * validation and result bits are fc_step's.  When `out` is given it holds the
+ * raw sum between the passes and the array is not used; otherwise the plan's
+ * extent (one past its last segment element) must be at most
+ * FC_NOALLOC_MAX_ELEMS, whatever the schedule (FC_ESIZE).  The current device
+ * must be the plan's (FC_EINVAL).  The call allocates no device or host
+ * memory and records no per-kernel timing; like every call it replaces a
+ * pointer table only when the pointers change.  Calls of TWO_PASS plans on
+ * one GPU use that GPU's one array: those that may run at the same time on
+ * one GPU (other plans, other streams or threads) race on it; calls on one
+ * plan are ordered (see the conventions above).  The array needs no clearing:
+ * the reduce pass writes every segment element before the update pass reads
+ * it. */
 #define FC_NOALLOC_MAX_ELEMS 16777216
 int fc_step_noalloc(fc_plan* plan, const void* const* grads, float* w, float* v, float lr, float mu,
                     float wd, int batch, float* out, float* const* bcast_dst, void* stream);

@@ -301,8 +301,8 @@ class Plan:
             raise FcError("fc_step", rc)
 
     def step_noalloc(self, grads, w, v, lr, mu, wd, batch, out=None, bcast=None, stream=None):
-        """fc_step_noalloc: the step in two passes with the raw sum in the
-        library's fixed device array (no allocation)."""
+        """fc_step_noalloc: the step without any allocation (a two-pass plan
+        keeps the raw sum in the library's fixed device array)."""
         g, wp, vp, op, bp = self._step_args(grads, w, v, out, bcast)
         rc = fc_step_noalloc(self.handle, g, wp, vp, lr, mu, wd, batch, op, bp, _stream(stream))
         if rc:

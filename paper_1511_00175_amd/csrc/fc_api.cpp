@@ -291,12 +291,16 @@ hipError_t take_event(fc_plan* p, hipEvent_t* e) {
     return hipEventCreate(e);
 }
 
-// Launch `go` on stream s; with timing on, bracket it with two events (not
-// while s is being captured: the plan's records would then name events that
-// only a graph records, so such a call is refused before anything is enqueued).
+// Whether fc_step is two launches (a split plan joins its passes in one).
+bool two_launches(const fc_plan* p) { return p->schedule == FC_SCHED_TWO_PASS && !p->shape.lane; }
+
+// Launch `go` on stream s; with timing on (and `timed`), bracket it with two
+// events (not while s is being captured: the plan's records would then name
+// events that only a graph records, so such a call is refused before anything
+// is enqueued).
 template <typename F>
-int launch(fc_plan* p, int kind, hipStream_t s, F&& go) {
-    if (!p->timing) return hip_rc(go());
+int launch(fc_plan* p, int kind, hipStream_t s, bool timed, F&& go) {
+    if (!timed || !p->timing) return hip_rc(go());
     const int crc = capture_check(s);
     if (crc) return crc;
     fc_plan::Rec r{nullptr, nullptr, kind};
@@ -757,7 +761,7 @@ static int fc_tree_reduce_body(fc_plan* p, const void* const* grads, float* out,
         a.grads = p->d_grads;
         a.K = p->K;
         a.out = out;
-        rc = launch(p, FC_KERNEL_REDUCE, s, [&] {
+        rc = launch(p, FC_KERNEL_REDUCE, s, true, [&] {
             return p->schedule == FC_SCHED_RESIDENT ? launch_resident(p, fc::MODE_REDUCE, a, s)
                                                     : launch_reduce(p->shape, fc::MODE_REDUCE, p->grid, a, s);
         });
@@ -792,7 +796,7 @@ static int fc_sgd_step_body(fc_plan* p, float* w, float* v, const float* g, floa
     a.mu = mu;
     a.wd = wd;
     a.c = 1.0f / static_cast<float>(batch);
-    rc = launch(p, FC_KERNEL_SGD, s, [&] { return fc::launch_sgd(p->shape, p->grid, a, s); });
+    rc = launch(p, FC_KERNEL_SGD, s, true, [&] { return fc::launch_sgd(p->shape, p->grid, a, s); });
     if (note) note_stream(p, s);
     return rc;
 }
@@ -819,7 +823,7 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
         a.src = src;
         a.dst = p->d_dst;
         a.K = p->K;
-        rc = launch(p, FC_KERNEL_BCAST, s, [&] {
+        rc = launch(p, FC_KERNEL_BCAST, s, true, [&] {
             if (p->schedule != FC_SCHED_RESIDENT) return fc::launch_bcast(p->shape, p->grid, a, s);
             // resident plans: the step's ranges, one launch per round, or
             // all rounds' ranges in one launch of grid x rounds blocks
@@ -868,9 +872,9 @@ int update_step_tables(fc_plan* p, const void* const* grads, float* const* bcast
 
 // Two passes on the plan's tiles: the reduce kernel stores the raw sum into
 // `sum`, then the SGD kernel updates w, v from it (and stores the broadcast
-// copies).  `sh` is the launch shape of both passes.
-int two_pass(fc_plan* p, const fc::Shape& sh, float* sum, float* w, float* v, float lr, float mu, float wd,
-             float c, bool bcast, hipStream_t s, bool timed) {
+// copies).
+int two_pass(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, float wd, float c, bool bcast,
+             hipStream_t s, bool timed) {
     fc::ReduceArgs r{};
     r.tiles = p->d_tiles;
     r.ntiles = p->ntiles;
@@ -891,13 +895,35 @@ int two_pass(fc_plan* p, const fc::Shape& sh, float* sum, float* w, float* v, fl
     g.mu = mu;
     g.wd = wd;
     g.c = c;
-    if (!timed) {
-        int rc = hip_rc(launch_reduce(sh, fc::MODE_REDUCE, p->grid, r, s));
-        return rc ? rc : hip_rc(fc::launch_sgd(sh, p->grid, g, s));
-    }
-    int rc = launch(p, FC_KERNEL_REDUCE, s, [&] { return launch_reduce(sh, fc::MODE_REDUCE, p->grid, r, s); });
-    if (rc == FC_OK) rc = launch(p, FC_KERNEL_SGD, s, [&] { return fc::launch_sgd(sh, p->grid, g, s); });
-    return rc;
+    const int rc = launch(p, FC_KERNEL_REDUCE, s, timed,
+                          [&] { return launch_reduce(p->shape, fc::MODE_REDUCE, p->grid, r, s); });
+    return rc ? rc : launch(p, FC_KERNEL_SGD, s, timed, [&] { return fc::launch_sgd(p->shape, p->grid, g, s); });
+}
+
+// A step in the plan's schedule, its pointer tables in place; `sum` is where
+// two passes keep the raw sum (two_launches).
+int run_step(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, float wd, int batch, float* out,
+             bool bcast, hipStream_t s, bool timed) {
+    const float c = 1.0f / static_cast<float>(batch);
+    if (two_launches(p)) return two_pass(p, sum, w, v, lr, mu, wd, c, bcast, s, timed);
+    fc::ReduceArgs a{};
+    a.tiles = p->d_tiles;
+    a.ntiles = p->ntiles;
+    a.mults = p->d_mults;
+    a.grads = p->d_grads;
+    a.K = p->K;
+    a.w = w;
+    a.v = v;
+    a.out = out;
+    a.dst = bcast ? p->d_dst : nullptr;
+    a.lr = lr;
+    a.mu = mu;
+    a.wd = wd;
+    a.c = c;
+    return launch(p, FC_KERNEL_STEP, s, timed, [&] {
+        return p->schedule == FC_SCHED_RESIDENT ? launch_resident(p, fc::MODE_STEP, a, s)
+                                                : launch_reduce(p->shape, fc::MODE_STEP, p->grid, a, s);
+    });
 }
 
 }  // namespace
@@ -912,38 +938,20 @@ static int fc_step_body(fc_plan* p, const void* const* grads, float* w, float* v
     rc = order_after_last(p, s, note);
     if (rc) return rc;
     rc = update_step_tables(p, grads, bcast_dst, s);
-    const float c = 1.0f / static_cast<float>(batch);
-    if (rc == FC_OK && p->schedule == FC_SCHED_TWO_PASS && !p->shape.lane) {
-        // pass 1: raw sum into `out` (or the plan's scratch); pass 2: update
-        // (+ broadcast).  On a split plan one launch does both passes' work.
-        rc = two_pass(p, p->shape, out ? out : p->d_sum, w, v, lr, mu, wd, c, bcast_dst != nullptr, s, true);
-    } else if (rc == FC_OK) {
-        fc::ReduceArgs a{};
-        a.tiles = p->d_tiles;
-        a.ntiles = p->ntiles;
-        a.mults = p->d_mults;
-        a.grads = p->d_grads;
-        a.K = p->K;
-        a.w = w;
-        a.v = v;
-        a.out = out;
-        a.dst = bcast_dst ? p->d_dst : nullptr;
-        a.lr = lr;
-        a.mu = mu;
-        a.wd = wd;
-        a.c = c;
-        rc = launch(p, FC_KERNEL_STEP, s, [&] {
-            return p->schedule == FC_SCHED_RESIDENT ? launch_resident(p, fc::MODE_STEP, a, s)
-                                                    : launch_reduce(p->shape, fc::MODE_STEP, p->grid, a, s);
-        });
-    }
+    // two passes: the raw sum goes into `out` or the plan's scratch
+    if (rc == FC_OK)
+        rc = run_step(p, out ? out : p->d_sum, w, v, lr, mu, wd, batch, out, bcast_dst != nullptr, s, true);
     if (note) note_stream(p, s);
     return rc;
 }
 
-// fc_step's two-pass schedule with the raw sum in the library's fixed device
-// array (fc_update.hip) instead of memory the plan owns; it allocates
-// nothing, on the device or on the host.
+// fc_step where a plan of two passes keeps the raw sum in the library's fixed
+// device array (fc_update.hip) instead of its own scratch; nothing is
+// allocated, on the device or on the host.  The other schedules keep the sum
+// on chip and run as they are: a reduce and an update pass in their place
+// read and wrote the sum once more and, on the resident plans' one-wave
+// tiles, reduced more slowly (measured on MI355X, us per call: 734016 x K=32
+// fp32 21.2 in two passes, 18.2 resident).
 static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, float* v, float lr, float mu,
                                 float wd, int batch, float* out, float* const* bcast_dst, void* stream) {
     int rc = check_step(p, grads, w, v, batch, out, bcast_dst);
@@ -953,17 +961,8 @@ static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, 
     if (hipGetDevice(&dev) != hipSuccess) return FC_EHIP;
     if (dev != p->device) return FC_EINVAL;
     if (p->ntiles == 0) return FC_OK;
-    // both passes run on the plan's tiles (block * vecs lane-vectors each);
-    // a resident plan's batch of 4 replicas has no reduce-kernel instance,
-    // so its reduce pass loads batches of 8 (the association does not depend
-    // on the batch)
-    fc::Shape sh = p->shape;
-    if (!sh.lane && !fc::compiled_pair(sh.vecs, sh.kchunk)) {
-        sh.kchunk = 8;
-        sh.maxd = bit_length(p->K / sh.kchunk);
-    }
     float* sum = out;
-    if (!sum) {
+    if (!sum && two_launches(p)) {
         rc = hip_rc(fc::noalloc_scratch(dev, &sum));
         if (rc) return rc;
     }
@@ -972,9 +971,7 @@ static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, 
     rc = order_after_last(p, s, note);
     if (rc) return rc;
     rc = update_step_tables(p, grads, bcast_dst, s);
-    if (rc == FC_OK)
-        rc = two_pass(p, sh, sum, w, v, lr, mu, wd, 1.0f / static_cast<float>(batch), bcast_dst != nullptr, s,
-                      false);
+    if (rc == FC_OK) rc = run_step(p, sum, w, v, lr, mu, wd, batch, out, bcast_dst != nullptr, s, false);
     if (note) note_stream(p, s);
     return rc;
 }
