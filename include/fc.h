@@ -134,7 +134,11 @@ typedef struct fc_plan fc_plan;
  *   that every call is one launch and the plan owns no raw-sum scratch.  Any
  *   other step of less than 64 MiB (n_elems * (K * bytes per element + 16))
  *   runs FUSED; a larger one RESIDENT when one round holds the plan or a
- *   parameter's replicas take at least 48 bytes, else FUSED.  With a
+ *   parameter's replicas take at least 48 bytes (32 from 2^25 parameters on),
+ *   else FUSED.  Such a RESIDENT plan of one round and at most 16 fp16 replicas
+ *   (8 beyond 2^23 parameters) reduces and steps in one pass over its tiles,
+ *   as FUSED does, unless the step broadcasts to more than 4 copies; its
+ *   one-pass launches leave no record for fc_plan_balance.  With a
  *   launch-shape field: TWO_PASS when they take more than 256 bytes, else
  *   FUSED. */
 typedef enum {
@@ -157,7 +161,7 @@ typedef enum {
  * at least 1024 tiles of 256 elements, (4, 4, 256) for fp16 with K <= 4 and at least
  * 4096 such tiles, else (1, 16, 64); otherwise (also with an explicit schedule
  * or shape field) fp16 -> (4 vectors, 4 replicas, 256
- * threads); fp32 with K <= 4 -> (1, 8, 256); fp32 with 16 < K <= 64 ->
+ * threads); fp32 with K <= 2 -> (1, 8, 256); fp32 with 16 < K <= 64 ->
  * (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the
  * streaming (nt) hint. */
 typedef struct {

@@ -42,6 +42,7 @@ struct fc_plan {
     int res_grid = 0;
     int res_rounds = 0;
     bool res_one_launch = false;     // every round in one launch (FC_SCHED_RESIDENT_ONE_LAUNCH)
+    bool res_one_pass = false;       // reduce and step run the reduce kernel on the tiles (fc::one_pass_f16)
     int res_lds = 0;                 // RESIDENT: LDS bytes per block
     int res_slot = 0;                // RESIDENT: LDS bytes per tile
     int res_in_regs = 0;             // RESIDENT: tiles per block held in registers
@@ -456,7 +457,7 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
                                                    tiles_of(32), tiles_of(16), sh);
     const bool resident = res_req || (choose && !split &&
                                       fc::default_resident(K, gdt == FC_F16 ? 2 : 4, static_cast<int64_t>(res_rounds),
-                                                           step_bytes));
+                                                           n_elems, step_bytes));
     if (choose && !split && !resident && step_bytes < fc::RESIDENT_MIN_BYTES)
         fc::short_shape(gdt, K, tiles_of(64), sh);
     if (resident) {
@@ -538,6 +539,7 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
         p->res_grid = res_grid;
         p->res_rounds = static_cast<int>(res_rounds);
         p->res_one_launch = sched_req == FC_SCHED_RESIDENT_ONE_LAUNCH;
+        p->res_one_pass = !res_req && gdt == FC_F16 && res_rounds == 1 && fc::one_pass_f16(K, n_elems);
         p->res_lds = static_cast<int>(res_lds);
         p->res_slot = static_cast<int>(slot_bytes);
         p->res_in_regs = static_cast<int>(in_regs);
@@ -762,8 +764,9 @@ static int fc_tree_reduce_body(fc_plan* p, const void* const* grads, float* out,
         a.K = p->K;
         a.out = out;
         rc = launch(p, FC_KERNEL_REDUCE, s, true, [&] {
-            return p->schedule == FC_SCHED_RESIDENT ? launch_resident(p, fc::MODE_REDUCE, a, s)
-                                                    : launch_reduce(p->shape, fc::MODE_REDUCE, p->grid, a, s);
+            return p->schedule == FC_SCHED_RESIDENT && !p->res_one_pass
+                       ? launch_resident(p, fc::MODE_REDUCE, a, s)
+                       : launch_reduce(p->shape, fc::MODE_REDUCE, p->grid, a, s);
         });
     }
     if (note) note_stream(p, s);
@@ -920,9 +923,11 @@ int run_step(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, flo
     a.mu = mu;
     a.wd = wd;
     a.c = c;
+    const bool one_pass =
+        p->schedule != FC_SCHED_RESIDENT || (p->res_one_pass && (!bcast || p->K <= fc::ONE_PASS_BCAST_K));
     return launch(p, FC_KERNEL_STEP, s, timed, [&] {
-        return p->schedule == FC_SCHED_RESIDENT ? launch_resident(p, fc::MODE_STEP, a, s)
-                                                : launch_reduce(p->shape, fc::MODE_STEP, p->grid, a, s);
+        return one_pass ? launch_reduce(p->shape, fc::MODE_STEP, p->grid, a, s)
+                        : launch_resident(p, fc::MODE_STEP, a, s);
     });
 }
 

@@ -14,22 +14,22 @@ namespace fc {
 
 // Launch-shape defaults, measured on MI355X for the five workloads:
 //   fp16 replicas       : 4 vectors per lane, 4 replicas per batch, 256 threads
-//   fp32, K <= 4        : 1 vector per lane, 8 replicas per batch, 256 threads
+//   fp32, K <= 2        : 1 vector per lane, 8 replicas per batch, 256 threads
 //   fp32, 16 < K <= 64  : 4 vectors per lane, 2 replicas per batch, 256 threads
 //   other fp32          : 1 vector per lane, 16 replicas per batch, 64 threads
 // Four vectors per lane make every wave read 4 KiB of one replica at a time,
 // which HBM serves better than 1 KiB pieces, as long as the lane's registers
 // (16 accumulators per pending subtree) still allow enough waves in flight.
-// With at most 4 replicas a step is short and launch-bound: 4x fewer,
-// larger blocks and a batch no larger than needed measured (2^20 parameters,
-// us per step, steps with w, v from HBM / 20-step HIP graph on one set,
-// against (1, 16, 64)): K=4 6.98-7.04 / 4.67-5.12 vs 7.58-7.79 / 4.79-5.10,
-// K=2 5.78 / 4.39 vs 5.98 / 4.59; from K=8 on no better (K=8 10.68 / 7.66
-// vs 10.55 / 8.09, K=16 16.47 / 14.44 vs 15.37 / 14.43).
+// With one or two replicas a wave has little to load: 4x fewer, larger blocks
+// measured 1.3-5% faster on large plans (4 10^7 parameters, us per step, (1, 8,
+// 256) vs (1, 16, 64): K=1 126.2 vs 127.6, K=2 155.9 vs 149.1 but its reduce
+// 74.4 vs 84.8); from K=3 on one wave per block wins in every call (K=3 step
+// 185.9 vs 176.4, broadcast 276 vs 261, reduce 105.7 vs 99.3; K=4 216 vs 203,
+// 341 vs 318, 134 vs 125).  Short steps have rules of their own (short_shape).
 inline void default_shape(fc_dtype gdt, int K, fc::Shape& sh) {
     if (gdt == FC_F16) {
         sh.vecs = 4; sh.kchunk = 4; sh.block = 256;
-    } else if (K <= 4) {
+    } else if (K <= 2) {
         sh.vecs = 1; sh.kchunk = 8; sh.block = 256;
     } else if (K > 16 && K <= 64) {
         sh.vecs = 4; sh.kchunk = 2; sh.block = 256;
@@ -189,10 +189,33 @@ inline bool compiled_pair(int u, int c) {
 // vs 15.0, fp16 2^20 x K=64 24.1 vs 26.4, 2^21 x K=8 15.2 vs 15.6, 200000 x
 // K=256 34.4 vs 34.2).
 constexpr uint64_t RESIDENT_MIN_BYTES = uint64_t(64) << 20;
-inline bool default_resident(int K, int bytes_per_element, int64_t rounds, uint64_t step_bytes) {
+// From 2^25 parameters on 32 bytes are enough: with paired loads, its own v'
+// write phase and register-held tiles the resident kernel wins there in every
+// call (measured on MI355X, us, fused vs resident: fp32 3.4 10^7 x K=8 step
+// 279 vs 270, broadcast 479 vs 460, x K=11 357 vs 322, 639 vs 595, 8 10^7 x
+// K=11 832 vs 783; fp16 8 10^7 x K=16 688 vs 640, 1729 vs 1571, 6.1 10^7 x K=16
+// reduce 382 vs 346; at 24 bytes, fp32 4 10^7 x K=6, 258 vs 264).  Smaller plans
+// of several rounds would gain as much, but keep the 48 bytes by which callers
+// and the tests know their schedule.
+constexpr uint64_t RESIDENT_MANY_ELEMS = uint64_t(1) << 25;
+inline bool default_resident(int K, int bytes_per_element, int64_t rounds, uint64_t n_elems, uint64_t step_bytes) {
     if (step_bytes < RESIDENT_MIN_BYTES) return false;
-    return rounds == 1 || static_cast<int64_t>(K) * bytes_per_element >= 48;
+    return rounds == 1 || static_cast<int64_t>(K) * bytes_per_element >= (n_elems >= RESIDENT_MANY_ELEMS ? 32 : 48);
 }
+
+// Calls that a default plan of one resident round runs in one pass, on the
+// same tiles, with the reduce kernel: with few fp16 replicas a parameter's
+// update moves as many bytes as its replicas, and a resident block's second
+// phase waits for its slowest wave.  Measured on MI355X (us, resident vs one
+// pass, steps): 2^22 x K=2 21.6 vs 16.2, x K=8 25.1 vs 22.4, x K=16 35.5 vs 32.6,
+// 2^23 x K=4 42.2 vs 32.2, x K=16 67.5 vs 61.3, 1.4 10^7 x K=4 60.8 vs 55.3, x K=8
+// 74.3 vs 73.2 (x K=12 92.2 vs 93.7, x K=16 106 vs 114; 2^23 x K=20 with the raw
+// sum 85.4 vs 87.6); reduce 2^23 x K=2 21.2 vs 17.0, x K=8 28.8 vs 27.9.  A
+// step's broadcast copies are written faster one destination at a time, but
+// with up to 4 of them one pass still wins (2^23 x K=2 52.7 vs 44.2, x K=4 68.8
+// vs 64.2, x K=8 96.9 vs 104).
+inline bool one_pass_f16(int K, uint64_t n_elems) { return K <= (n_elems <= (uint64_t(1) << 23) ? 16 : 8); }
+constexpr int ONE_PASS_BCAST_K = 4;
 
 // Resident launches record each block's rate (for fc_plan_balance) when a
 // block's share of a round is at least this many tiles.  Measured on
