@@ -162,7 +162,7 @@ int order_after_last(fc_plan* p, hipStream_t s, bool& note) {
 // graph: the graph would record a copy from the plan's host buffer, which
 // later calls overwrite, so a capture may only hold calls that keep the
 // tables.  `host` has its size from plan creation on (nothing is allocated
-// here): K entries and SPLIT_PAD more, which repeat the last one for kernels
+// here): K entries and TABLE_PAD more, which repeat the last one for kernels
 // that read whole batches of pointers.
 template <typename P>
 int update_table(fc_plan* p, std::vector<P>& host, bool& valid, P* dev, const P* want, hipStream_t s) {
@@ -515,8 +515,8 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
                 tiles.push_back(t);
             }
         }
-        p->h_grads.assign(K + fc::SPLIT_PAD, nullptr);
-        p->h_dst.assign(K + fc::SPLIT_PAD, nullptr);
+        p->h_grads.assign(K + fc::TABLE_PAD, nullptr);
+        p->h_dst.assign(K + fc::TABLE_PAD, nullptr);
     } catch (const std::bad_alloc&) {
         delete p;
         return FC_ENOMEM;
@@ -827,7 +827,7 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
         a.dst = p->d_dst;
         a.K = p->K;
         rc = launch(p, FC_KERNEL_BCAST, s, true, [&] {
-            if (p->schedule != FC_SCHED_RESIDENT) return fc::launch_bcast(p->shape, p->grid, a, s);
+            if (p->schedule != FC_SCHED_RESIDENT) return fc::launch_bcast(p->shape, p->grid, p->grid < p->ntiles, a, s);
             // resident plans: the step's ranges, one launch per round, or
             // all rounds' ranges in one launch of grid x rounds blocks
             // (block b takes range b of the whole table)

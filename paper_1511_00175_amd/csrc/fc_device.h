@@ -220,6 +220,34 @@ __device__ __forceinline__ void st32r(gptr_w_t base, uint32_t off, const float* 
     }
 }
 
+// Values x to destinations [k0, k1) of K at the lane's byte offset, V per lane.
+// With K >= 16, or where blocks share the destinations, the pointers are read 8
+// at a time (the table is padded past the last one): one scalar load per store,
+// which each store had to wait for, bounded the copies of short plans (measured
+// on MI355X, us, before / now with the destinations also shared among blocks:
+// broadcast 4096 x K=1000 46.3 / 4.2, 16384 x K=600 28.6 / 7.3; step with
+// broadcast 23.8 / 10.2, 18.1 / 12.0).  Fewer are stored one by one, which
+// larger plans, bounded by the writes, prefer (4 10^7 x K=3 102.4 vs 104.2,
+// 10^6 x K=8 step 12.6 vs 12.8).
+template <int V>
+__device__ __forceinline__ void st32_copies(float* const* dst, int k0, int k1, int K, uint64_t start4,
+                                            uint32_t off, const float* x) {
+    constexpr int B = 8;
+    static_assert(B <= TABLE_PAD, "pointers are read in whole batches");
+    if (K < 2 * B && k1 - k0 == K) {
+        for (int k = k0; k < k1; ++k) st32r<V>(gwrite(ldc(dst, k)) + start4, off, x);
+        return;
+    }
+    for (int k = k0; k < k1; k += B) {
+        gptr_w_t d[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) d[j] = gwrite(ldc(dst, k + j)) + start4;
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if (k + j < k1) st32r<V>(d[j], off, x);
+    }
+}
+
 // V fp32 values at byte offset `off`, read once (streaming policy)
 template <int V> __device__ __forceinline__ void ld32s(gptr_t base, uint32_t off, float* x) {
     if constexpr (V == 1) {
@@ -476,8 +504,7 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a, uint64_t start,
             st32r<V>(gwrite(a.w) + start4, off[u], wn);
             st32r<V>(gwrite(a.v) + start4, off[u], vn);
             if (a.out) st32r<V>(gwrite(a.out) + start4, off[u], s.a[u]);
-            if (a.dst)
-                for (int k = 0; k < a.K; ++k) st32r<V>(gwrite(ldc(a.dst, k)) + start4, off[u], wn);
+            if (a.dst) st32_copies<V>(a.dst, 0, a.K, a.K, start4, off[u], wn);
         }
     }
 }
@@ -499,18 +526,17 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
     }
 }
 
-// The end of the work on one lane-vector whose raw sum s[0..V-1] is known:
-// reduce-only, store the sum; step, update w and v and store w', v' (and the
-// raw sum and the broadcast copies when asked for).  KEEP (the resident
-// kernel): with a broadcast, leave w' in keep[0..V-1] instead of storing the
-// copies; without one, store w' and leave v' in keep[0..V-1] instead of
-// storing it, for the caller to store after the block's w' stores (measured
-// on MI355X with both builds alternated in one process, us per step: VGG-19
-// K=16 1763.3 vs 1775.5, GoogLeNet 536.5 vs 537.7, NiN and AlexNet fp16
-// unchanged).  The caller's keep may alias s.
-template <int V, int MODE, bool KEEP = false, int CP = CPOL_RESULT_STORE>
+// The end of a resident block's work on one lane-vector whose raw sum s[0..V-1]
+// is known: reduce-only, store the sum; step, update w and v and store w' (and
+// the raw sum when asked for).  With a broadcast, v' is stored too and w' left
+// in keep[0..V-1] for the copies; without one, v' is left there, for the
+// caller to store after the block's w' stores (measured on MI355X with both
+// builds alternated in one process, us per step: VGG-19 K=16 1763.3 vs 1775.5,
+// GoogLeNet 536.5 vs 537.7, NiN and AlexNet fp16 unchanged).  keep may alias s.
+template <int V, int MODE>
 __device__ __forceinline__ void finish(const ReduceArgs& a, uint64_t start4, uint32_t off, const float* s,
-                                       float lr_j, float wd_j, float* keep = nullptr) {
+                                       float lr_j, float wd_j, float* keep) {
+    constexpr int CP = CPOL_RESIDENT_STORE;
     if constexpr (MODE == MODE_REDUCE) {
         st32r<V, CP>(gwrite(a.out) + start4, off, s);
     } else {
@@ -520,19 +546,10 @@ __device__ __forceinline__ void finish(const ReduceArgs& a, uint64_t start4, uin
 #pragma unroll
         for (int i = 0; i < V; ++i) sgd1(s[i], w[i], v[i], lr_j, a.mu, wd_j, a.c, wn[i], vn[i]);
         st32r<V, CP>(gwrite(a.w) + start4, off, wn);
-        if (!KEEP || a.dst) st32r<V, CP>(gwrite(a.v) + start4, off, vn);
+        if (a.dst) st32r<V, CP>(gwrite(a.v) + start4, off, vn);
         if (a.out) st32r<V, CP>(gwrite(a.out) + start4, off, s);
-        if constexpr (KEEP) {
-            if (a.dst) {
 #pragma unroll
-                for (int i = 0; i < V; ++i) keep[i] = wn[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < V; ++i) keep[i] = vn[i];
-            }
-        } else if (a.dst) {
-            for (int k = 0; k < a.K; ++k) st32r<V, CP>(gwrite(ldc(a.dst, k)) + start4, off, wn);
-        }
+        for (int i = 0; i < V; ++i) keep[i] = a.dst ? wn[i] : vn[i];
     }
 }
 
@@ -587,8 +604,10 @@ __device__ __forceinline__ void store_slots(const WaveTiles& own, int first, flo
     constexpr int SLOT = RESIDENT_SLOT * U;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint32_t lane = threadIdx.x & 63;
+    gptr_w_t next = gwrite(ldc(dst, 0));
     for (int k = 0; k < K; ++k) {
-        const gptr_w_t d = gwrite(ldc(dst, k));
+        const gptr_w_t d = next;
+        next = gwrite(ldc(dst, k + 1));  // the table is padded past the last one
         extra(d);
         for (int j = q, i = first; j < n; j += W, ++i) {
             const Tile tile = own.at(i);
@@ -661,20 +680,20 @@ __device__ __forceinline__ void finish_kept(const ReduceArgs& a, const Tile& til
             for (int u = 0; u < U; ++u) {
                 const uint32_t e0 = 256 * u + 2 * lane, e1 = e0 + 128;
                 if (e0 < ne)
-                    finish<2, MODE, true, CPOL_RESIDENT_STORE>(a, start4, e0 * 4, &x.a[u][0], lr_j, wd_j, &x.a[u][0]);
+                    finish<2, MODE>(a, start4, e0 * 4, &x.a[u][0], lr_j, wd_j, &x.a[u][0]);
                 if (e1 < ne)
-                    finish<2, MODE, true, CPOL_RESIDENT_STORE>(a, start4, e1 * 4, &x.a[u][2], lr_j, wd_j, &x.a[u][2]);
+                    finish<2, MODE>(a, start4, e1 * 4, &x.a[u][2], lr_j, wd_j, &x.a[u][2]);
             }
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t vi = lane + 64 * u;
                 if (vi < tile.count)
-                    finish<4, MODE, true, CPOL_RESIDENT_STORE>(a, start4, vi * 16, x.a[u], lr_j, wd_j, x.a[u]);
+                    finish<4, MODE>(a, start4, vi * 16, x.a[u], lr_j, wd_j, x.a[u]);
             }
         }
     } else if (lane < tile.count) {
-        finish<1, MODE, true, CPOL_RESIDENT_STORE>(a, start4, lane * 4, &x.a[0][0], lr_j, wd_j, &x.a[0][0]);
+        finish<1, MODE>(a, start4, lane * 4, &x.a[0][0], lr_j, wd_j, &x.a[0][0]);
     }
 }
 
@@ -820,11 +839,10 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
                 for (int u = 0; u < U; ++u) {
                     const uint32_t vi = lane + 64 * u;
                     if (vi < tile.count)
-                        finish<4, MODE, true, CPOL_RESIDENT_STORE>(a, start4, vi * 16, slot + vi * 4, lr_j, wd_j,
-                                                               slot + vi * 4);
+                        finish<4, MODE>(a, start4, vi * 16, slot + vi * 4, lr_j, wd_j, slot + vi * 4);
                 }
             } else if (lane < tile.count) {
-                finish<1, MODE, true, CPOL_RESIDENT_STORE>(a, start4, lane * 4, slot + lane, lr_j, wd_j, slot + lane);
+                finish<1, MODE>(a, start4, lane * 4, slot + lane, lr_j, wd_j, slot + lane);
             }
         }
         if constexpr (MODE == MODE_STEP) {
@@ -889,8 +907,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& a, uint64_t start, uint3
         for (int i = 0; i < V; ++i) sgd1(g[i], w[i], v[i], lr_j, a.mu, wd_j, a.c, wn[i], vn[i]);
         st32r<V>(gwrite(a.w) + start4, off, wn);
         st32r<V>(gwrite(a.v) + start4, off, vn);
-        if (a.dst)
-            for (int k = 0; k < a.K; ++k) st32r<V>(gwrite(ldc(a.dst, k)) + start4, off, wn);
+        if (a.dst) st32_copies<V>(a.dst, 0, a.K, a.K, start4, off, wn);
     }
 }
 
@@ -908,7 +925,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(SgdArgs a) {
 
 // ------------------------------------------------------------------ broadcast
 template <int V, int U>
-__device__ __forceinline__ void bcast_body(const BcastArgs& a, uint64_t start, uint32_t count) {
+__device__ __forceinline__ void bcast_body(const BcastArgs& a, uint64_t start, uint32_t count, int k0, int k1) {
     uint32_t idx[U];
     bool act[U];
     lane_elems<V, U>(count, idx, act);
@@ -919,16 +936,18 @@ __device__ __forceinline__ void bcast_body(const BcastArgs& a, uint64_t start, u
         const uint32_t off = idx[u] * 4;
         float x[V];
         ld32s<V>(gread(a.src) + start4, off, x);
-        for (int k = 0; k < a.K; ++k) st32r<V>(gwrite(ldc(a.dst, k)) + start4, off, x);
+        st32_copies<V>(a.dst, k0, k1, a.K, start4, off, x);
     }
 }
 
 template <int V, int U>
 __global__ __launch_bounds__(256) void bcast_kernel(BcastArgs a) {
+    const int k0 = static_cast<int>(blockIdx.y) * a.per;
+    const int k1 = k0 + a.per < a.K ? k0 + a.per : a.K;
     for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         const Tile tile = ld_tile(a.tiles, t);
-        if (!(tile.seg & TAIL_BIT)) bcast_body<V, U>(a, tile.start, tile.count * (4 / V));
-        else bcast_body<1, 1>(a, tile.start, tile.count);
+        if (!(tile.seg & TAIL_BIT)) bcast_body<V, U>(a, tile.start, tile.count * (4 / V), k0, k1);
+        else bcast_body<1, 1>(a, tile.start, tile.count, k0, k1);
     }
 }
 

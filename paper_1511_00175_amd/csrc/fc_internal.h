@@ -21,6 +21,10 @@ struct Tile {
 };
 static_assert(sizeof(Tile) == 16, "Tile is loaded as one 16-byte scalar load");
 
+// Readable entries of a pointer table past the last one (they repeat it):
+// kernels read whole batches of pointers.
+constexpr int TABLE_PAD = 16;
+
 constexpr uint32_t TAIL_BIT = 0x80000000u;
 constexpr uint32_t SEG_MASK = 0x7fffffffu;
 
@@ -74,7 +78,6 @@ constexpr int RESIDENT_CLOCK_WORDS = 4;
 constexpr int RESIDENT_SLOT = 256;  // floats per tile of 64 lanes x one 4-element vector
 constexpr int RESIDENT_WAVES = 16;
 constexpr int SPLIT_WAVES = 16;     // most waves that share a tile (split_kernel)
-constexpr int SPLIT_PAD = 16;       // readable entries of a replica table past the last replica
 
 struct SgdArgs {
     const Tile* tiles;
@@ -94,6 +97,7 @@ struct BcastArgs {
     const float* src;
     float* const* dst;
     int K;
+    int per;                      // destinations per block of bcast_kernel (blockIdx.y times per is its first)
     const int* ranges;            // resident plans: gridDim.x + 1 tile indices of one round
     int slots;                    // resident plans: LDS tile slots per block (>= 1)
 };
@@ -107,7 +111,7 @@ hipError_t launch_reduce_f16(const Shape& sh, int mode, int grid, const ReduceAr
 hipError_t launch_split_f32(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s);
-hipError_t launch_bcast(const Shape& sh, int grid, const BcastArgs& a, hipStream_t s);
+hipError_t launch_bcast(const Shape& sh, int grid, bool capped, BcastArgs a, hipStream_t s);
 hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, const BcastArgs& a, hipStream_t s);
 hipError_t prepare_resident_bcast(const Shape& sh, size_t lds);
 hipError_t prepare_resident_f32(const Shape& sh, size_t lds);

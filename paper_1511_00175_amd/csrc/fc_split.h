@@ -61,7 +61,7 @@ constexpr int SPLIT_C = 16;     // replicas per batch
 constexpr int SPLIT_MAXD = 3;   // pending-subtree stack: runs of up to 4 batches
 
 // The wave's vector of replicas [k, k + n), n <= SPLIT_C (nothing for n <= 0).
-// All pointers are read first, at once (the table holds SPLIT_PAD readable
+// All pointers are read first, at once (the table holds TABLE_PAD readable
 // entries past the last replica), and the loads go out in groups of 4; the
 // surplus of the last group re-reads the last replica.
 template <int DT, int V>
@@ -239,9 +239,9 @@ __device__ __forceinline__ void split_tile(const ReduceArgs& a, int run, float* 
             // thread e alone
             if (own) lds[e] = wn;
             __syncthreads();
+            const int per = (a.K + nw - 1) / nw, k0 = q * per;  // the wave's destinations
             if (lane * V < ne)
-                for (int k = q; k < a.K; k += nw)
-                    st32r<V>(gwrite(ldc(a.dst, k)) + start4, lane * V * 4, lds + lane * V);
+                st32_copies<V>(a.dst, k0, k0 + per < a.K ? k0 + per : a.K, a.K, start4, lane * V * 4, lds + lane * V);
         }
     }
 }

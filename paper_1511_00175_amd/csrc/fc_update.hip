@@ -1,6 +1,7 @@
 // SGD-from-a-raw-sum and broadcast kernels: one block per tile, one thread
 // per lane of the tile; on resident plans the broadcast runs one persistent
 // block per CU.
+#include <algorithm>
 #include <mutex>
 
 #include "fc_device.h"
@@ -34,12 +35,10 @@ hipError_t noalloc_scratch(int device, float** ptr) {
 
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s) {
     if (sh.lane) {  // tiles of 64 lanes x sh.lane elements
-        auto narrow = [&](auto v) {
+        return pick<1, 2>(sh.lane, [&](auto v) {
             hipLaunchKernelGGL((sgd_kernel<v.value, 1>), dim3(grid), dim3(64), 0, s, a);
             return hipGetLastError();
-        };
-        if (sh.lane == 4) return narrow(I<4>{});
-        return pick<1, 2>(sh.lane, narrow);
+        });
     }
     auto go = [&](auto u) {
         hipLaunchKernelGGL((sgd_kernel<4, u.value>), dim3(grid), dim3(sh.block), 0, s, a);
@@ -49,21 +48,23 @@ hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s
     return pick<1, 2>(sh.vecs, go);
 }
 
-hipError_t launch_bcast(const Shape& sh, int grid, const BcastArgs& a, hipStream_t s) {
-    if (sh.lane) {  // tiles of 64 lanes x sh.lane elements
-        auto narrow = [&](auto v) {
-            hipLaunchKernelGGL((bcast_kernel<v.value, 1>), dim3(grid), dim3(64), 0, s, a);
-            return hipGetLastError();
-        };
-        if (sh.lane == 4) return narrow(I<4>{});
-        return pick<1, 2>(sh.lane, narrow);
-    }
-    auto go = [&](auto u) {
-        hipLaunchKernelGGL((bcast_kernel<4, u.value>), dim3(grid), dim3(sh.block), 0, s, a);
+// Plans of few tiles share the destinations among blocks, so that at least
+// BCAST_WAVES waves store, each of them to 8 destinations or more.
+constexpr int BCAST_WAVES = 4096;
+
+hipError_t launch_bcast(const Shape& sh, int grid, bool capped, BcastArgs a, hipStream_t s) {
+    const int block = sh.lane ? 64 : sh.block;
+    const int waves = grid * (block / 64);
+    const int groups = capped ? 1 : std::max(1, std::min((a.K + 7) / 8, (BCAST_WAVES + waves - 1) / std::max(1, waves)));
+    a.per = (a.K + groups - 1) / groups;
+    const dim3 blocks(grid, (a.K + a.per - 1) / a.per);
+    auto go = [&](auto v, auto u) {
+        hipLaunchKernelGGL((bcast_kernel<v.value, u.value>), blocks, dim3(block), 0, s, a);
         return hipGetLastError();
     };
-    if (sh.vecs == 4) return go(I<4>{});
-    return pick<1, 2>(sh.vecs, go);
+    if (sh.lane) return pick<1, 2>(sh.lane, [&](auto v) { return go(v, I<1>{}); });  // 64 lanes x sh.lane elements
+    if (sh.vecs == 4) return go(I<4>{}, I<4>{});
+    return pick<1, 2>(sh.vecs, [&](auto u) { return go(I<4>{}, u); });
 }
 
 // The resident broadcast for a plan's resident tile shape (1 or 2 lane

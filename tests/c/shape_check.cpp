@@ -97,7 +97,7 @@ int main() {
                         CHECK((sh.waves - 1) * 16 < K || sh.waves == sh.lane, "K=%d waves %d", K, sh.waves);
                     }
                     // the last batch starts at a replica: its pointers end inside the pad
-                    CHECK((K - 1) / 16 * 16 + 15 < K + fc::SPLIT_PAD, "pad for K=%d", K);
+                    CHECK((K - 1) / 16 * 16 + 15 < K + fc::TABLE_PAD, "pad for K=%d", K);
                 }
             }
         }
