@@ -89,6 +89,8 @@ def _rows(x):
 _TORCH_DTYPES = {"f32": "float32", "f16": "float16"}
 
 
+_lib_step, _lib_step_noalloc = _fc.lib.fc_step, _fc.lib.fc_step_noalloc
+
 _STEP_CACHE = 64  # sets of step buffers whose checks are kept per plan
 
 
@@ -276,12 +278,15 @@ class Plan:
         cache = self._step_cache
         hit = cache.get(key) if cache is not None else None
         if hit is not None:
-            refs, sigs, got = hit
-            if (refs[0]() is grads and refs[1]() is w and refs[2]() is v
-                    and (out is None if refs[3] is None else refs[3]() is out)
-                    and (bcast is None if refs[4] is None else refs[4]() is bcast)
-                    and sigs == (_sig(grads), _sig(w), _sig(v), out is not None and _sig(out),
-                                 bcast is not None and _sig(bcast))):
+            rg, rw, rv, ro, rb, sg, sw, sv, so, sb, got = hit
+            # the signatures as _sig gives them, written out: a call each
+            # costs a tenth of a short step's host time
+            if (rg() is grads and rw() is w and rv() is v
+                    and sw == (w.data_ptr(), w.shape, w.stride(), w.dtype, w.get_device())
+                    and sv == (v.data_ptr(), v.shape, v.stride(), v.dtype, v.get_device())
+                    and sg == (grads.data_ptr(), grads.shape, grads.stride(), grads.dtype, grads.get_device())
+                    and (out is None if ro is None else ro() is out and so == _sig(out))
+                    and (bcast is None if rb is None else rb() is bcast and sb == _sig(bcast))):
                 return got
         got = (self._grads(grads), self._vec(w, "w"), self._vec(v, "v"), self._vec(out, "out", optional=True),
                None if bcast is None else self._reps(bcast, "bcast", "float32"))
@@ -289,14 +294,14 @@ class Plan:
         if all(b is None or type(b).__name__ in ("Tensor", "Parameter") for b in bufs) and grads is not None:
             if cache is None or len(cache) >= _STEP_CACHE:
                 cache = self._step_cache = {}
-            cache[key] = (tuple(None if b is None else weakref.ref(b) for b in bufs),
-                          (_sig(grads), _sig(w), _sig(v), out is not None and _sig(out),
-                           bcast is not None and _sig(bcast)), got)
+            cache[key] = (*(None if b is None else weakref.ref(b) for b in bufs),
+                          *(None if b is None else _sig(b) for b in bufs), got)
         return got
 
     def step(self, grads, w, v, lr, mu, wd, batch, out=None, bcast=None, stream=None):
         g, wp, vp, op, bp = self._step_args(grads, w, v, out, bcast)
-        rc = fc_step(self.handle, g, wp, vp, lr, mu, wd, batch, op, bp, _stream(stream))
+        # the buffers are C arrays and addresses already: straight to the library
+        rc = _lib_step(self.handle, g, wp, vp, lr, mu, wd, int(batch), op, bp, _stream(stream))
         if rc:
             raise FcError("fc_step", rc)
 
@@ -304,6 +309,6 @@ class Plan:
         """fc_step_noalloc: the step without any allocation (a two-pass plan
         keeps the raw sum in the library's fixed device array)."""
         g, wp, vp, op, bp = self._step_args(grads, w, v, out, bcast)
-        rc = fc_step_noalloc(self.handle, g, wp, vp, lr, mu, wd, batch, op, bp, _stream(stream))
+        rc = _lib_step_noalloc(self.handle, g, wp, vp, lr, mu, wd, int(batch), op, bp, _stream(stream))
         if rc:
             raise FcError("fc_step_noalloc", rc)

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "fc.h"
+#include "fc_alias.h"
 #include "fc_internal.h"
 #include "fc_partition.h"
 #include "fc_shape.h"
@@ -73,46 +74,16 @@ struct fc_plan {
 
 namespace {
 
-constexpr int K_MAX = 1024;
+constexpr int K_MAX = fc::ALIAS_K_MAX;
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-struct Span {
-    uintptr_t lo, hi;  // [lo, hi)
-    int id;            // distinct buffer id; replicas share role 0 and differ by id
-    bool written;
-    bool replica;
-};
-
-// The buffers one call names (at most K replicas, K destinations and four
-// more), held on the caller's stack so that validation allocates nothing.
-struct Spans {
-    static constexpr int CAP = 2 * K_MAX + 4;
-    Span v[CAP];
-    int n = 0;
-    void push(const Span& x) { v[n++] = x; }
-};
-
-// Written buffers may not overlap any other buffer, except that `out` may be
-// exactly a replica of an FC_F32 plan (each element is read by the thread
-// that writes it).  Read-only buffers may overlap each other.  The spans are
-// sorted by start and each is compared only with the spans that start
-// before it ends, so a valid call costs O(n log n) for n = K + a few spans.
-int check_aliasing(Spans& sp, int out_id, bool f32) {
-    Span* spans = sp.v;
-    const size_t n =
-        static_cast<size_t>(std::remove_if(spans, spans + sp.n, [](const Span& x) { return x.hi == x.lo; }) - spans);
-    std::sort(spans, spans + n, [](const Span& x, const Span& y) { return x.lo < y.lo; });
-    for (size_t i = 0; i < n; ++i) {
-        const Span& a = spans[i];
-        for (size_t j = i + 1; j < n && spans[j].lo < a.hi; ++j) {
-            const Span& b = spans[j];  // overlaps a: b.lo >= a.lo and b.lo < a.hi
-            if (!a.written && !b.written) continue;
-            const bool exact_out_alias =
-                f32 && ((a.id == out_id && b.replica) || (b.id == out_id && a.replica)) && a.lo == b.lo &&
-                a.hi == b.hi;
-            if (!exact_out_alias) return FC_EALIAS;
-        }
+// K pointers that must be there and aligned.
+template <typename P> int check_pointers(const fc_plan* p, P const* ptrs) {
+    if (!ptrs) return FC_EINVAL;
+    for (int k = 0; k < p->K; ++k) {
+        if (!ptrs[k]) return FC_EINVAL;
+        if (!aligned16(ptrs[k])) return FC_EALIGN;
     }
     return FC_OK;
 }
@@ -711,31 +682,13 @@ static int fc_plan_read_timing_body(fc_plan* p, fc_timing* t) {
 
 namespace {
 
-// Byte extent of a buffer of `elem` bytes per element covering the plan.
-Span span_of(const fc_plan* p, const void* ptr, int elem, bool written, int id, bool replica) {
-    const uintptr_t lo = reinterpret_cast<uintptr_t>(ptr);
-    return Span{lo, lo + static_cast<uintptr_t>(p->extent) * elem, id, written, replica};
-}
-
-enum { ID_W = 1, ID_V, ID_OUT, ID_G, ID_SRC, ID_REPLICA0 = 16 };
-
-int check_replicas(const fc_plan* p, const void* const* grads, Spans& spans) {
-    if (!grads) return FC_EINVAL;
-    for (int k = 0; k < p->K; ++k) {
-        if (!grads[k]) return FC_EINVAL;
-        if (!aligned16(grads[k])) return FC_EALIGN;
-        spans.push(span_of(p, grads[k], p->sg, false, ID_REPLICA0 + k, true));
-    }
-    return FC_OK;
-}
-
-int check_dsts(const fc_plan* p, float* const* dst, Spans& spans) {
-    for (int k = 0; k < p->K; ++k) {
-        if (!dst[k]) return FC_EINVAL;
-        if (!aligned16(dst[k])) return FC_EALIGN;
-        spans.push(span_of(p, dst[k], 4, true, ID_REPLICA0 + p->K + k, false));
-    }
-    return FC_OK;
+// The buffers a call names, for the overlap check (fc_alias.h).
+fc::AliasCall buffers_of(const fc_plan* p) {
+    fc::AliasCall c;
+    c.K = p->K;
+    c.rep_bytes = static_cast<uintptr_t>(p->extent) * p->sg;
+    c.f32_bytes = static_cast<uintptr_t>(p->extent) * 4;
+    return c;
 }
 
 }  // namespace
@@ -743,12 +696,13 @@ int check_dsts(const fc_plan* p, float* const* dst, Spans& spans) {
 static int fc_tree_reduce_body(fc_plan* p, const void* const* grads, float* out, void* stream) {
     if (!p || !out) return FC_EINVAL;
     if (!aligned16(out)) return FC_EALIGN;
-    Spans spans;
-    int rc = check_replicas(p, grads, spans);
+    int rc = check_pointers(p, grads);
     if (rc) return rc;
-    spans.push(span_of(p, out, 4, true, ID_OUT, false));
-    rc = check_aliasing(spans, ID_OUT, p->gdt == FC_F32);
-    if (rc) return rc;
+    fc::AliasCall c = buffers_of(p);
+    c.grads = grads;
+    c.out = c.others;
+    c.add(out, true);
+    if (fc::aliased(c)) return FC_EALIAS;
     if (p->ntiles == 0) return FC_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     bool note = false;
@@ -777,16 +731,15 @@ static int fc_sgd_step_body(fc_plan* p, float* w, float* v, const float* g, floa
                 void* stream) {
     if (!p || !w || !v || !g || batch < 1) return FC_EINVAL;
     if (!aligned16(w) || !aligned16(v) || !aligned16(g)) return FC_EALIGN;
-    Spans spans;
-    spans.push(span_of(p, w, 4, true, ID_W, false));
-    spans.push(span_of(p, v, 4, true, ID_V, false));
-    spans.push(span_of(p, g, 4, false, ID_G, false));
-    int rc = check_aliasing(spans, -1, false);
-    if (rc) return rc;
+    fc::AliasCall c = buffers_of(p);
+    c.add(w, true);
+    c.add(v, true);
+    c.add(g, false);
+    if (fc::aliased(c)) return FC_EALIAS;
     if (p->ntiles == 0) return FC_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     bool note = false;
-    rc = order_after_last(p, s, note);
+    int rc = order_after_last(p, s, note);
     if (rc) return rc;
     fc::SgdArgs a{};
     a.tiles = p->d_tiles;
@@ -807,12 +760,12 @@ static int fc_sgd_step_body(fc_plan* p, float* w, float* v, const float* g, floa
 static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, void* stream) {
     if (!p || !src || !dst) return FC_EINVAL;
     if (!aligned16(src)) return FC_EALIGN;
-    Spans spans;
-    spans.push(span_of(p, src, 4, false, ID_SRC, false));
-    int rc = check_dsts(p, dst, spans);
+    int rc = check_pointers(p, dst);
     if (rc) return rc;
-    rc = check_aliasing(spans, -1, false);
-    if (rc) return rc;
+    fc::AliasCall c = buffers_of(p);
+    c.dst = dst;
+    c.add(src, false);
+    if (fc::aliased(c)) return FC_EALIAS;
     if (p->ntiles == 0) return FC_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     bool note = false;
@@ -853,17 +806,19 @@ int check_step(const fc_plan* p, const void* const* grads, float* w, float* v, i
                float* const* bcast_dst) {
     if (!p || !w || !v || batch < 1) return FC_EINVAL;
     if (!aligned16(w) || !aligned16(v) || (out && !aligned16(out))) return FC_EALIGN;
-    Spans spans;
-    int rc = check_replicas(p, grads, spans);
+    int rc = check_pointers(p, grads);
+    if (rc == FC_OK && bcast_dst) rc = check_pointers(p, bcast_dst);
     if (rc) return rc;
-    spans.push(span_of(p, w, 4, true, ID_W, false));
-    spans.push(span_of(p, v, 4, true, ID_V, false));
-    if (out) spans.push(span_of(p, out, 4, true, ID_OUT, false));
-    if (bcast_dst) {
-        rc = check_dsts(p, bcast_dst, spans);
-        if (rc) return rc;
+    fc::AliasCall c = buffers_of(p);
+    c.grads = grads;
+    c.dst = bcast_dst;
+    c.add(w, true);
+    c.add(v, true);
+    if (out) {
+        c.out = c.others;
+        c.add(out, true);
     }
-    return check_aliasing(spans, out ? ID_OUT : -1, p->gdt == FC_F32);
+    return fc::aliased(c) ? FC_EALIAS : FC_OK;
 }
 
 // The replica table, and the destination table when broadcasting.
