@@ -424,7 +424,7 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     const bool choose = sched_req == FC_SCHED_AUTO && !shape_given;
     // tiles of 256, 128 and 64 elements: is the plan too short to fill the
     // chip with one wave per tile?
-    const bool split = choose && fc::default_split(gdt, order == FC_ORDER_TREE, K, std::max(1, cus), tiles_of(64),
+    const bool split = choose && fc::default_split(gdt, order == FC_ORDER_TREE, K, std::max(1, cus), lds_cu, tiles_of(64),
                                                    tiles_of(32), tiles_of(16), sh);
     const bool resident = res_req || (choose && !split &&
                                       fc::default_resident(K, gdt == FC_F16 ? 2 : 4, static_cast<int64_t>(res_rounds),
@@ -531,6 +531,9 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
               hipMalloc(reinterpret_cast<void**>(&p->d_dst), p->h_dst.size() * sizeof(float*)) == hipSuccess;
     if (ok && p->schedule == FC_SCHED_TWO_PASS && !split && p->extent > 0)
         ok = hipMalloc(&p->d_sum, static_cast<size_t>(p->extent) * sizeof(float)) == hipSuccess;
+    if (ok && split && sh.chain)
+        ok = (gdt == FC_F16 ? fc::prepare_chain_f16(static_cast<size_t>(lds_cu))
+                            : fc::prepare_chain_f32(static_cast<size_t>(lds_cu))) == hipSuccess;
     if (ok && resident) {
         const size_t clock_bytes = static_cast<size_t>(res_grid) * fc::RESIDENT_CLOCK_WORDS * sizeof(unsigned long long);
         ok = hipMalloc(reinterpret_cast<void**>(&p->d_ranges), ranges.size() * sizeof(int)) == hipSuccess &&

@@ -43,6 +43,7 @@ struct Shape {
     int lane;
     int waves;
     int run;
+    int chain;        // 1: the chain kernel (linear order), wave 0 adds what the others load
 };
 
 struct ReduceArgs {
@@ -109,6 +110,8 @@ constexpr int MAXD_MAX = 10;
 hipError_t launch_reduce_f32(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_reduce_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_split_f32(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
+hipError_t prepare_chain_f32(size_t lds);
+hipError_t prepare_chain_f16(size_t lds);
 hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s);
 hipError_t launch_bcast(const Shape& sh, int grid, bool capped, BcastArgs a, hipStream_t s);

@@ -12,6 +12,8 @@ hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArg
     return launch_split_dt<FC_F16>(sh, mode, grid, a, s);
 }
 
+hipError_t prepare_chain_f16(size_t lds) { return prepare_chain_dt<FC_F16>(lds); }
+
 hipError_t launch_resident_f16(const Shape& sh, int mode, int grid, size_t lds, const ResidentArgs& a,
                                hipStream_t s) {
     return launch_resident_dt<FC_F16>(sh, mode, grid, lds, a, s);

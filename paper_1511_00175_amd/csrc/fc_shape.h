@@ -108,6 +108,17 @@ inline void short_shape(fc_dtype gdt, int K, uint64_t tiles256, fc::Shape& sh) {
     }
 }
 
+// The chain kernel (linear order, at most one tile per unit: wave 0 adds what the
+// others load) from this many replicas on, and the LDS of its two buffers.  A
+// dependent addition takes about 7 ns here, so the serial chain is what is left;
+// with fewer replicas the wave that does not load costs more than it saves.
+// Measured on MI355X (us per call in a graph, split / chain): fp32 8274 x K=1000
+// 13.5 / 12.2, 4096 x K=1000 12.1 / 10.3, 16384 x K=1000 14.4 / 13.9, 8000 x K=900
+// with broadcast 16.2 / 14.1, fp16 4096 x K=700 10.2 / 9.3; 4096 x K=512 6.3 / 6.6,
+// 16384 x K=128 3.4 / 3.7.
+constexpr int CHAIN_MIN_K = 640;
+constexpr int CHAIN_LDS = 2 * (SPLIT_WAVES - 1) * 16 * 64 * 4;
+
 // The split kernel (a tile is a block's work, its waves share the replicas)
 // for plans of at most 6 tiles of 256 elements per compute unit (5 for fp16 in
 // linear order, where the one wave that adds has the most to do): one wave per
@@ -134,7 +145,7 @@ inline void short_shape(fc_dtype gdt, int K, uint64_t tiles256, fc::Shape& sh) {
 // of two: more only wait for the one that adds (fp16 200000 x K=128 with 2 / 4
 // waves 10.9 / 12.9, 2^16 x K=1000 with 4 / 8 24.6 / 22.2); the batches of all
 // waves fit 64 KiB of LDS.
-inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, uint64_t tiles256, uint64_t tiles128,
+inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, int lds_cu, uint64_t tiles256, uint64_t tiles128,
                           uint64_t tiles64, fc::Shape& sh) {
     const uint64_t cu = static_cast<uint64_t>(cus);
     const uint64_t most = !tree && gdt == FC_F16 ? 5 : 6;
@@ -148,6 +159,10 @@ inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, uint64_t tile
         if (many) sh.run = 32;
         while (sh.run < 64 && (K + sh.run - 1) / sh.run > (many ? SPLIT_WAVES / 2 : SPLIT_WAVES)) sh.run *= 2;
         sh.waves = (K + sh.run - 1) / sh.run;
+    } else if (K >= CHAIN_MIN_K && tiles64 <= cu && lds_cu >= CHAIN_LDS) {
+        sh.lane = 1;
+        sh.chain = 1;
+        sh.waves = 1 + std::min(batches, SPLIT_WAVES - 1);
     } else {
         const uint64_t budget = (gdt == FC_F16 ? 32 : 16) * cu;
         sh.waves = SPLIT_WAVES / sh.lane;

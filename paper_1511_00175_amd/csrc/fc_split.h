@@ -111,6 +111,8 @@ template <int N, int T> __device__ __forceinline__ float tree_of_waves(const flo
 template <int T, int B> __device__ __forceinline__ void chain_read(const float* p, float (&x)[B]) {
 #pragma unroll
     for (int j = 0; j < B; ++j) x[j] = p[j * T];
+    // the scheduler would move these reads down to their first use
+    __builtin_amdgcn_sched_barrier(0);
 }
 template <int B> __device__ __forceinline__ float chain_add(float acc, const float (&x)[B]) {
 #pragma unroll
@@ -266,8 +268,103 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void split_kernel(ReduceArgs a, i
     }
 }
 
+// Linear order where a tile has a compute unit to itself: the additions' serial
+// chain is then all there is, so wave 0 does nothing else.  The other waves put
+// batches of SPLIT_C replicas into one of two LDS buffers, one barrier per
+// buffer, while wave 0 adds the other one.  Tiles of 64 elements; element e is
+// lane e of wave 0.  What is left is the additions' latency: 1000 of them take
+// about 7 us (8274 x K=1000 fp32 12.2 us per step, of which 2.5 an empty launch;
+// 13.5 with waves that load and add in turn); two batches per wave on their way
+// instead of one, 32 values read from LDS at a time instead of 16, or one wait
+// for each batch of reads changed nothing.
+template <int DT, int MODE>
+__global__ __launch_bounds__(64 * SPLIT_WAVES) void chain_kernel(ReduceArgs a) {
+    extern __shared__ f4 slot_vecs[];
+    float* lds = reinterpret_cast<float*>(slot_vecs);
+    constexpr uint32_t SG = DT == FC_F16 ? 2 : 4;
+    constexpr int T = 64;
+    const int q = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int nw = static_cast<int>(blockDim.x) / 64;
+    const int per = (nw - 1) * SPLIT_C;  // replicas per buffer
+    const int row = (q - 1) * SPLIT_C;   // of a loading wave
+    const uint32_t lane = threadIdx.x & 63;
+    for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+        const Tile tile = ld_tile(a.tiles, t);
+        const uint32_t ne = tile.seg & TAIL_BIT ? tile.count : tile.count * 4;
+        const uint64_t start4 = tile.start * 4;
+        const bool own = lane < ne;
+        const uint32_t e = own ? lane : 0u;
+        float lr_j = 0.0f, wd_j = 0.0f, w = 0.0f, v = 0.0f;
+        typename Rep<DT, 1>::raw r[SPLIT_C];
+        if (q) {
+            load_batch<DT, 1>(a.grads, row, a.K - row, tile.start * SG, e * SG, r);
+        } else if constexpr (MODE == MODE_STEP) {
+            const int j = static_cast<int>(tile.seg & SEG_MASK);
+            lr_j = a.lr * ldc(a.mults, 2 * j);
+            wd_j = a.wd * ldc(a.mults, 2 * j + 1);
+            ld32s<1>(gread(a.w) + start4, e * 4, &w);
+            ld32s<1>(gread(a.v) + start4, e * 4, &v);
+        }
+        float s = -0.0f;  // -0 + x is x, whatever x
+        float* buf = lds;
+        for (int c0 = 0; c0 < a.K; c0 += per) {
+            if (q) {
+#pragma unroll
+                for (int j = 0; j < SPLIT_C; ++j) Rep<DT, 1>::widen(r[j], &buf[(row + j) * T + lane]);
+                const int k1 = c0 + per + row;
+                load_batch<DT, 1>(a.grads, k1, a.K - k1, tile.start * SG, e * SG, r);
+            }
+            // wave 0 added the buffer that is filled next before it came here
+            __syncthreads();
+            if (!q) s = chain<T, SPLIT_C>(buf + lane, a.K - c0 < per ? a.K - c0 : per, s);
+            buf = buf == lds ? lds + per * T : lds;
+        }
+        if constexpr (MODE == MODE_REDUCE) {
+            if (!q && own) st32r<1>(gwrite(a.out) + start4, e * 4, &s);
+        } else {
+            float wn, vn;
+            sgd1(s, w, v, lr_j, a.mu, wd_j, a.c, wn, vn);
+            if (!q && own) {
+                st32r<1>(gwrite(a.w) + start4, e * 4, &wn);
+                st32r<1>(gwrite(a.v) + start4, e * 4, &vn);
+                if (a.out) st32r<1>(gwrite(a.out) + start4, e * 4, &s);
+            }
+            if (a.dst) {
+                __syncthreads();  // buffers done with
+                if (!q) lds[lane] = wn;
+                __syncthreads();
+                const int n = (a.K + nw - 1) / nw, k0 = q * n;  // the wave's destinations
+                if (own) st32_copies<1>(a.dst, k0, k0 + n < a.K ? k0 + n : a.K, a.K, start4, e * 4, lds + lane);
+            }
+        }
+        __syncthreads();  // the next tile overwrites the LDS
+    }
+}
+
+inline size_t chain_lds(const Shape& sh) {
+    return sizeof(float) * 64 * 2 * SPLIT_C * (sh.waves - 1);
+}
+
+// Allow the chain kernel `lds` bytes of dynamic LDS (a property of the kernel,
+// set when a plan that runs it is created).
+template <int DT> hipError_t prepare_chain_dt(size_t lds) {
+    for (const void* kernel : {reinterpret_cast<const void*>(&chain_kernel<DT, MODE_REDUCE>),
+                               reinterpret_cast<const void*>(&chain_kernel<DT, MODE_STEP>)}) {
+        const hipError_t e =
+            hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int DT>
 hipError_t launch_split_dt(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s) {
+    if (sh.chain) {
+        return pick<MODE_REDUCE, MODE_STEP>(mode, [&](auto md) {
+            hipLaunchKernelGGL((chain_kernel<DT, md.value>), dim3(grid), dim3(64 * sh.waves), chain_lds(sh), s, a);
+            return hipGetLastError();
+        });
+    }
     const size_t lds = sizeof(float) * 64 * sh.lane * sh.waves * (sh.tree ? 1 : SPLIT_C);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * sh.waves), lds, s, a, sh.run);

@@ -75,7 +75,7 @@ int main() {
                 for (int is_tree = 0; is_tree < 2; ++is_tree) {
                     fc::Shape sh{};
                     const uint64_t n128 = (n64 + 1) / 2, n256 = (n64 + 3) / 4;
-                    if (!fc::default_split(f16 ? FC_F16 : FC_F32, is_tree, K, cus, n256, n128, n64, sh)) {
+                    if (!fc::default_split(f16 ? FC_F16 : FC_F32, is_tree, K, cus, 160 << 10, n256, n128, n64, sh)) {
                         CHECK(sh.lane == 0, "lane without the kernel");
                         continue;
                     }
@@ -92,6 +92,9 @@ int main() {
                             sums.push_back(run_sum(&x[q * sh.run], std::min(sh.run, K - q * sh.run)));
                         const float got = tree(sums);
                         CHECK(std::memcmp(&got, &want, 4) == 0, "K=%d run %d: %a for %a", K, sh.run, got, want);
+                    } else if (sh.chain) {
+                        CHECK(sh.lane == 1 && sh.waves >= 2 && n64 <= (uint64_t)cus, "chain of %d waves", sh.waves);
+                        CHECK(2 * (sh.waves - 1) * 16 * 64 * 4 <= fc::CHAIN_LDS && fc::CHAIN_LDS <= 160 << 10, "LDS");
                     } else {
                         CHECK(sizeof(float) * 64 * sh.lane * sh.waves * 16 <= 65536, "LDS of %d x %d", sh.lane, sh.waves);
                         CHECK((sh.waves - 1) * 16 < K || sh.waves == sh.lane, "K=%d waves %d", K, sh.waves);

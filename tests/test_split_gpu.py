@@ -39,7 +39,7 @@ def tiles(rows, width):
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("order", ["tree", "linear"])
-@pytest.mark.parametrize("K", [17, 31, 33, 48, 128, 129, 256, 257, 512, 513, 1000, 1024])
+@pytest.mark.parametrize("K", [17, 31, 33, 48, 128, 129, 256, 257, 512, 513, 639, 640, 1000, 1024])
 def test_narrow_tiles_match_oracle(fc, K, order, dtype):
     p = fc.Plan(NARROW, K, dtype, order)
     info = p.info()
