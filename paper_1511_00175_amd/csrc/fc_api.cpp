@@ -783,7 +783,7 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
         a.dst = p->d_dst;
         a.K = p->K;
         rc = launch(p, FC_KERNEL_BCAST, s, true, [&] {
-            if (p->schedule != FC_SCHED_RESIDENT) return fc::launch_bcast(p->shape, p->grid, p->grid < p->ntiles, a, s);
+            if (p->schedule != FC_SCHED_RESIDENT) return fc::launch_bcast(p->shape, p->grid, p->grid < p->ntiles, p->n_elems, a, s);
             // resident plans: the step's ranges, one launch per round, or
             // all rounds' ranges in one launch of grid x rounds blocks
             // (block b takes range b of the whole table)

@@ -220,24 +220,41 @@ __device__ __forceinline__ void st32r(gptr_w_t base, uint32_t off, const float* 
     }
 }
 
-// Values x to destinations [k0, k1) of K at the lane's byte offset, V per lane.
-// With K >= 16, or where blocks share the destinations, the pointers are read 8
-// at a time (the table is padded past the last one): one scalar load per store,
-// which each store had to wait for, bounded the copies of short plans (measured
-// on MI355X, us, before / now with the destinations also shared among blocks:
-// broadcast 4096 x K=1000 46.3 / 4.2, 16384 x K=600 28.6 / 7.3; step with
-// broadcast 23.8 / 10.2, 18.1 / 12.0).  Fewer are stored one by one, which
-// larger plans, bounded by the writes, prefer (4 10^7 x K=3 102.4 vs 104.2,
-// 10^6 x K=8 step 12.6 vs 12.8).
+// V values just loaded, in their registers from here on.  Without this the
+// compiler leaves the wait for the load inside the loop of stores that follows,
+// where it waits for every earlier store as well (one counter serves loads and
+// stores), and the stores go out one round trip after another.  Measured on
+// MI355X, us, wait inside / before the loop: broadcast 8000 x K=8 3.97 / 2.29,
+// fp16 plans' 2^20 x K=4 6.82 / 4.61, 2 10^7 x K=8 150.4 / 141.1.
+template <int V> __device__ __forceinline__ void settle(float* x) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) asm volatile("" : "+v"(x[i]));
+}
+
+// Values x to the K destinations at the lane's byte offset, V per lane.  PACED:
+// each store waits for the one before it, which large plans of one-wave blocks
+// want, whose writes otherwise crowd each other (measured on MI355X, us, not
+// paced / paced: 2 10^7 fp32 x K=4 75 / 69, x K=8 144 / 136, x K=15 253 / 246,
+// 3 10^6 x K=12 30.9 / 28.2, 10^6 x K=4 4.3 / 4.8; K=3 and K=16 the same).
+template <int V, bool PACED = false>
+__device__ __forceinline__ void st32_copies(float* const* dst, int K, uint64_t start4, uint32_t off, const float* x) {
+    for (int k = 0; k < K; ++k) {
+        if constexpr (PACED) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        st32r<V>(gwrite(ldc(dst, k)) + start4, off, x);
+    }
+}
+
+// The same to destinations [k0, k1), where waves share the destinations of
+// their values: the pointers are read 8 at a time (the table is padded past the
+// last one), because on a chip of few waves one scalar load per store, which
+// each store had to wait for, bounds the copies (measured on MI355X, us, one by
+// one / shared: broadcast 4000 x K=1000 47.1 / 4.4, 16384 x K=200 10.8 / 3.3,
+// 65536 x K=64 14.0 / 4.7).
 template <int V>
-__device__ __forceinline__ void st32_copies(float* const* dst, int k0, int k1, int K, uint64_t start4,
-                                            uint32_t off, const float* x) {
+__device__ __forceinline__ void st32_copies_shared(float* const* dst, int k0, int k1, uint64_t start4, uint32_t off,
+                                                   const float* x) {
     constexpr int B = 8;
     static_assert(B <= TABLE_PAD, "pointers are read in whole batches");
-    if (K < 2 * B && k1 - k0 == K) {
-        for (int k = k0; k < k1; ++k) st32r<V>(gwrite(ldc(dst, k)) + start4, off, x);
-        return;
-    }
     for (int k = k0; k < k1; k += B) {
         gptr_w_t d[B];
 #pragma unroll
@@ -504,7 +521,7 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a, uint64_t start,
             st32r<V>(gwrite(a.w) + start4, off[u], wn);
             st32r<V>(gwrite(a.v) + start4, off[u], vn);
             if (a.out) st32r<V>(gwrite(a.out) + start4, off[u], s.a[u]);
-            if (a.dst) st32_copies<V>(a.dst, 0, a.K, a.K, start4, off[u], wn);
+            if (a.dst) st32_copies<V>(a.dst, a.K, start4, off[u], wn);
         }
     }
 }
@@ -907,7 +924,7 @@ __device__ __forceinline__ void sgd_body(const SgdArgs& a, uint64_t start, uint3
         for (int i = 0; i < V; ++i) sgd1(g[i], w[i], v[i], lr_j, a.mu, wd_j, a.c, wn[i], vn[i]);
         st32r<V>(gwrite(a.w) + start4, off, wn);
         st32r<V>(gwrite(a.v) + start4, off, vn);
-        if (a.dst) st32_copies<V>(a.dst, 0, a.K, a.K, start4, off, wn);
+        if (a.dst) st32_copies<V>(a.dst, a.K, start4, off, wn);
     }
 }
 
@@ -924,7 +941,7 @@ __global__ __launch_bounds__(256) void sgd_kernel(SgdArgs a) {
 }
 
 // ------------------------------------------------------------------ broadcast
-template <int V, int U>
+template <int V, int U, int COPIES>
 __device__ __forceinline__ void bcast_body(const BcastArgs& a, uint64_t start, uint32_t count, int k0, int k1) {
     uint32_t idx[U];
     bool act[U];
@@ -936,18 +953,22 @@ __device__ __forceinline__ void bcast_body(const BcastArgs& a, uint64_t start, u
         const uint32_t off = idx[u] * 4;
         float x[V];
         ld32s<V>(gread(a.src) + start4, off, x);
-        st32_copies<V>(a.dst, k0, k1, a.K, start4, off, x);
+        settle<V>(x);
+        if constexpr (COPIES == COPIES_SHARED) st32_copies_shared<V>(a.dst, k0, k1, start4, off, x);
+        else st32_copies<V, COPIES == COPIES_PACED>(a.dst, a.K, start4, off, x);
     }
 }
 
-template <int V, int U>
+// A tile is one block's, or (COPIES_SHARED) each block of a column (blockIdx.y)
+// has a.per of its destinations.
+template <int V, int U, int COPIES>
 __global__ __launch_bounds__(256) void bcast_kernel(BcastArgs a) {
-    const int k0 = static_cast<int>(blockIdx.y) * a.per;
+    const int k0 = COPIES == COPIES_SHARED ? static_cast<int>(blockIdx.y) * a.per : 0;
     const int k1 = k0 + a.per < a.K ? k0 + a.per : a.K;
     for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         const Tile tile = ld_tile(a.tiles, t);
-        if (!(tile.seg & TAIL_BIT)) bcast_body<V, U>(a, tile.start, tile.count * (4 / V), k0, k1);
-        else bcast_body<1, 1>(a, tile.start, tile.count, k0, k1);
+        if (!(tile.seg & TAIL_BIT)) bcast_body<V, U, COPIES>(a, tile.start, tile.count * (4 / V), k0, k1);
+        else bcast_body<1, 1, COPIES>(a, tile.start, tile.count, k0, k1);
     }
 }
 

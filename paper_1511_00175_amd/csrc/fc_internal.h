@@ -92,6 +92,9 @@ struct SgdArgs {
     float lr, mu, wd, c;
 };
 
+// How a block of bcast_kernel stores its values to the destinations.
+enum Copies { COPIES_IN_TURN = 0, COPIES_PACED = 1, COPIES_SHARED = 2 };
+
 struct BcastArgs {
     const Tile* tiles;
     int ntiles;
@@ -114,7 +117,7 @@ hipError_t prepare_chain_f32(size_t lds);
 hipError_t prepare_chain_f16(size_t lds);
 hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s);
-hipError_t launch_bcast(const Shape& sh, int grid, bool capped, BcastArgs a, hipStream_t s);
+hipError_t launch_bcast(const Shape& sh, int grid, bool capped, uint64_t n_elems, BcastArgs a, hipStream_t s);
 hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, const BcastArgs& a, hipStream_t s);
 hipError_t prepare_resident_bcast(const Shape& sh, size_t lds);
 hipError_t prepare_resident_f32(const Shape& sh, size_t lds);

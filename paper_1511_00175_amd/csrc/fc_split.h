@@ -242,8 +242,13 @@ __device__ __forceinline__ void split_tile(const ReduceArgs& a, int run, float* 
             if (own) lds[e] = wn;
             __syncthreads();
             const int per = (a.K + nw - 1) / nw, k0 = q * per;  // the wave's destinations
-            if (lane * V < ne)
-                st32_copies<V>(a.dst, k0, k0 + per < a.K ? k0 + per : a.K, a.K, start4, lane * V * 4, lds + lane * V);
+            if (lane * V < ne) {
+                float x[V];
+#pragma unroll
+                for (int i = 0; i < V; ++i) x[i] = lds[lane * V + i];
+                settle<V>(x);
+                st32_copies_shared<V>(a.dst, k0, k0 + per < a.K ? k0 + per : a.K, start4, lane * V * 4, x);
+            }
         }
     }
 }
@@ -334,7 +339,11 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void chain_kernel(ReduceArgs a) {
                 if (!q) lds[lane] = wn;
                 __syncthreads();
                 const int n = (a.K + nw - 1) / nw, k0 = q * n;  // the wave's destinations
-                if (own) st32_copies<1>(a.dst, k0, k0 + n < a.K ? k0 + n : a.K, a.K, start4, e * 4, lds + lane);
+                if (own) {
+                    float x = lds[lane];
+                    settle<1>(&x);
+                    st32_copies_shared<1>(a.dst, k0, k0 + n < a.K ? k0 + n : a.K, start4, e * 4, &x);
+                }
             }
         }
         __syncthreads();  // the next tile overwrites the LDS

@@ -52,14 +52,25 @@ hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s
 // BCAST_WAVES waves store, each of them to 8 destinations or more.
 constexpr int BCAST_WAVES = 4096;
 
-hipError_t launch_bcast(const Shape& sh, int grid, bool capped, BcastArgs a, hipStream_t s) {
+// Large plans of one-wave blocks pace their stores (see st32_copies).
+constexpr uint64_t PACED_MIN_ELEMS = uint64_t(1) << 21;
+
+hipError_t launch_bcast(const Shape& sh, int grid, bool capped, uint64_t n_elems, BcastArgs a, hipStream_t s) {
     const int block = sh.lane ? 64 : sh.block;
     const int waves = grid * (block / 64);
     const int groups = capped ? 1 : std::max(1, std::min((a.K + 7) / 8, (BCAST_WAVES + waves - 1) / std::max(1, waves)));
     a.per = (a.K + groups - 1) / groups;
     const dim3 blocks(grid, (a.K + a.per - 1) / a.per);
+    const bool paced = !sh.lane && block == 64 && sh.vecs == 1 && a.K >= 4 && a.K < 16 && n_elems >= PACED_MIN_ELEMS;
+    if (paced && blocks.y == 1) {
+        hipLaunchKernelGGL((bcast_kernel<4, 1, COPIES_PACED>), blocks, dim3(block), 0, s, a);
+        return hipGetLastError();
+    }
     auto go = [&](auto v, auto u) {
-        hipLaunchKernelGGL((bcast_kernel<v.value, u.value>), blocks, dim3(block), 0, s, a);
+        if (blocks.y > 1)
+            hipLaunchKernelGGL((bcast_kernel<v.value, u.value, COPIES_SHARED>), blocks, dim3(block), 0, s, a);
+        else
+            hipLaunchKernelGGL((bcast_kernel<v.value, u.value, COPIES_IN_TURN>), blocks, dim3(block), 0, s, a);
         return hipGetLastError();
     };
     if (sh.lane) return pick<1, 2>(sh.lane, [&](auto v) { return go(v, I<1>{}); });  // 64 lanes x sh.lane elements
