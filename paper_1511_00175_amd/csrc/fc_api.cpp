@@ -40,6 +40,7 @@ struct fc_plan {
     float* d_sum = nullptr;          // raw-sum scratch of the two-pass schedule (extent floats)
     int schedule = FC_SCHED_FUSED;   // resolved schedule of fc_step
     int* d_ranges = nullptr;         // RESIDENT: tile range of each block in each round (res_grid * res_rounds + 1)
+    bool capped = false;             // the caller limits the grid (max_blocks)
     int res_grid = 0;
     int res_rounds = 0;
     bool res_one_launch = false;     // every round in one launch (FC_SCHED_RESIDENT_ONE_LAUNCH)
@@ -498,7 +499,8 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     }
     p->ntiles = static_cast<int>(tiles.size());
     int grid = p->ntiles;
-    if (opts && opts->max_blocks > 0) grid = std::min(grid, opts->max_blocks);
+    p->capped = opts && opts->max_blocks > 0;
+    if (p->capped) grid = std::min(grid, opts->max_blocks);
     p->grid = grid;
 
     // fc_step schedule (see fc_schedule)
@@ -783,7 +785,10 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
         a.dst = p->d_dst;
         a.K = p->K;
         rc = launch(p, FC_KERNEL_BCAST, s, true, [&] {
-            if (p->schedule != FC_SCHED_RESIDENT) return fc::launch_bcast(p->shape, p->grid, p->grid < p->ntiles, p->n_elems, a, s);
+            if (p->schedule != FC_SCHED_RESIDENT)
+                return fc::launch_bcast(p->shape, p->grid,
+                                        fc::bcast_groups(p->shape, p->K, p->grid, p->n_elems, p->capped), p->n_elems,
+                                        a, s);
             // resident plans: the step's ranges, one launch per round, or
             // all rounds' ranges in one launch of grid x rounds blocks
             // (block b takes range b of the whole table)

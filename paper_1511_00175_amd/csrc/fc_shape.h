@@ -176,6 +176,25 @@ inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, int lds_cu, u
     return true;
 }
 
+// How many blocks share a tile's destinations in fc_broadcast on a plan that is
+// not resident (1: the tile is one block's).  With few waves on the chip they
+// are shared, at least 8 a block, until about 4096 waves store; with more the
+// copies are bounded by the writes, and sharing makes them slower.  The split
+// kernel's tiles have one wave each and K > 16 destinations; there the line is
+// 2^18 elements.  Measured on MI355X, us, one block / shared, destinations in
+// the Infinity Cache | not: 131072 x K=64 (128 waves) 15.1 / 6.1 | 14.9 / 6.8,
+// 262144 x K=64 (256 waves) 15.8 / 9.7 | 15.6 / 13.4, 400000 x K=64 (391) 17.1 /
+// 14.7 | 21.3 / 25.3, 600000 x K=64 19.9 / 20.4 | 28.9 / 37.8, 10^6 x K=16 9.3 /
+// 9.3 | 14.6 / 16.7; one-wave blocks 100000 x K=200 (391) 11.7 / 11.7 | 12.3 /
+// 14.5.
+// A grid that the caller capped stays as it is: the cap holds for every launch.
+constexpr int BCAST_WAVES = 4096, BCAST_SHARE_WAVES = 256;
+inline int bcast_groups(const Shape& sh, int K, int grid, uint64_t n_elems, bool capped) {
+    const int64_t waves = std::max<int64_t>(1, sh.lane ? grid : static_cast<int64_t>(grid) * (sh.block / 64));
+    if (capped || n_elems > (uint64_t(1) << 18) || (!sh.lane && waves > BCAST_SHARE_WAVES)) return 1;
+    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((K + 7) / 8, (BCAST_WAVES + waves - 1) / waves)));
+}
+
 inline bool compiled_pair(int u, int c) {
     return (u == 1 && (c == 8 || c == 16)) || (u == 2 && (c == 8 || c == 16)) ||
            (u == 4 && (c == 2 || c == 4 || c == 8));

@@ -1,7 +1,6 @@
 // SGD-from-a-raw-sum and broadcast kernels: one block per tile, one thread
 // per lane of the tile; on resident plans the broadcast runs one persistent
 // block per CU.
-#include <algorithm>
 #include <mutex>
 
 #include "fc_device.h"
@@ -48,17 +47,11 @@ hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s
     return pick<1, 2>(sh.vecs, go);
 }
 
-// Plans of few tiles share the destinations among blocks, so that at least
-// BCAST_WAVES waves store, each of them to 8 destinations or more.
-constexpr int BCAST_WAVES = 4096;
-
 // Large plans of one-wave blocks pace their stores (see st32_copies).
 constexpr uint64_t PACED_MIN_ELEMS = uint64_t(1) << 21;
 
-hipError_t launch_bcast(const Shape& sh, int grid, bool capped, uint64_t n_elems, BcastArgs a, hipStream_t s) {
+hipError_t launch_bcast(const Shape& sh, int grid, int groups, uint64_t n_elems, BcastArgs a, hipStream_t s) {
     const int block = sh.lane ? 64 : sh.block;
-    const int waves = grid * (block / 64);
-    const int groups = capped ? 1 : std::max(1, std::min((a.K + 7) / 8, (BCAST_WAVES + waves - 1) / std::max(1, waves)));
     a.per = (a.K + groups - 1) / groups;
     const dim3 blocks(grid, (a.K + a.per - 1) / a.per);
     const bool paced = !sh.lane && block == 64 && sh.vecs == 1 && a.K >= 4 && a.K < 16 && n_elems >= PACED_MIN_ELEMS;

@@ -1,0 +1,60 @@
+// CPU check of the rules by which calls choose their launches (csrc/fc_shape.h),
+// run by tests/test_rules_cpu.py: `rules_check NAME` checks one rule at the sizes
+// where it was measured and over its range.
+#include <cstdio>
+#include <cstring>
+
+#include "fc_shape.h"
+
+static int failures = 0;
+#define CHECK(c, ...)                                \
+    do {                                             \
+        if (!(c)) {                                  \
+            if (failures++ < 20) {                   \
+                std::fprintf(stderr, __VA_ARGS__);   \
+                std::fprintf(stderr, " [%s]\n", #c); \
+            }                                        \
+        }                                            \
+    } while (0)
+
+static fc::Shape shape(int block, int vecs, int lane = 0) {
+    fc::Shape sh{};
+    sh.block = block;
+    sh.vecs = vecs;
+    sh.lane = lane;
+    return sh;
+}
+
+// blocks that share a broadcast tile's destinations
+static void copies() {
+    const fc::Shape u4 = shape(256, 4), one = shape(64, 1), split = shape(512, 1, 1);
+    auto tiles = [](uint64_t n, uint64_t per) { return static_cast<int>((n + per - 1) / per); };
+    for (int K = 1; K <= 1024; ++K)
+        for (uint64_t n : {1000ull, 65536ull, 131072ull, 262144ull, 300000ull, 600000ull, 1000000ull, 3000000ull})
+            for (const fc::Shape& sh : {u4, one, split}) {
+                const int grid = tiles(n, sh.lane ? 64 * sh.lane : sh.block * sh.vecs * 4);
+                const int g = fc::bcast_groups(sh, K, grid, n, false);
+                CHECK(g >= 1 && g <= (K + 7) / 8, "K=%d n=%llu: %d", K, (unsigned long long)n, g);
+                // a caller's cap holds, also where it is wider than the grid
+                CHECK(fc::bcast_groups(sh, K, grid, n, true) == 1, "capped K=%d", K);
+                // writes bound the copies of larger plans
+                CHECK(n <= 262144 || g == 1, "K=%d n=%llu: %d", K, (unsigned long long)n, g);
+            }
+    CHECK(fc::bcast_groups(one, 1000, tiles(4000, 256), 4000, false) == 125, "4000 x K=1000");
+    CHECK(fc::bcast_groups(u4, 64, tiles(262144, 4096), 262144, false) == 8, "262144 x K=64");
+    CHECK(fc::bcast_groups(one, 200, tiles(100000, 256), 100000, false) == 1, "100000 x K=200");
+}
+
+int main(int, char** argv) {
+    const struct {
+        const char* name;
+        void (*run)();
+    } rules[] = {{"copies", copies}};
+    for (const auto& r : rules)
+        if (!std::strcmp(argv[1], r.name)) {
+            r.run();
+            if (!failures) std::printf("%s: as measured\n", r.name);
+            return failures ? 1 : 0;
+        }
+    return 2;
+}
