@@ -794,10 +794,12 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
             // (block b takes range b of the whole table)
             a.slots = p->res_lds / p->res_slot;
             const int per_launch = p->res_one_launch ? p->res_rounds : 1;
+            const bool packed =
+                fc::bcast_packed(p->K, p->ntiles, static_cast<int64_t>(p->res_grid) * p->res_rounds);
             for (int round = 0; round < p->res_rounds; round += per_launch) {
                 a.ranges = p->d_ranges + static_cast<size_t>(round) * p->res_grid;
                 const hipError_t e = fc::launch_resident_bcast(p->shape, p->res_grid * per_launch,
-                                                               static_cast<size_t>(p->res_lds), a, s);
+                                                               static_cast<size_t>(p->res_lds), packed, a, s);
                 if (e != hipSuccess) return e;
             }
             return hipSuccess;

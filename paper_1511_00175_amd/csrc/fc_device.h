@@ -570,20 +570,34 @@ __device__ __forceinline__ void finish(const ReduceArgs& a, uint64_t start4, uin
     }
 }
 
-// The descriptors of the tiles of one wave of a resident block, tile i (the
-// block's tile q + W i) in lane i: one load per round and wave instead of one
-// scalar load per tile, phase and broadcast copy, each of which the wave had to
-// wait for before it could ask for the tile's data.  Measured on MI355X (us per
-// call, a load per tile / per round, both builds alternated): fp16 6.1 10^7 x
-// K=16 reduce 353.0 / 339.4, NiN K=32 with broadcast 338.8 / 337.0, GoogLeNet
-// K=16 reduce, update and broadcast 184.5 / 183.7, GoogLeNet K=128, VGG-19 and
-// 2^20 to 2^23 x K=8 to 32 steps within 0.2%.
+// The descriptors of the tiles of one wave of a resident block (the wave's tile
+// i is tile t of the plan), read where they are needed, one scalar load each ...
+template <int W, bool PACKED> struct WaveTiles {
+    const Tile* tiles;
+    __device__ __forceinline__ WaveTiles(const Tile* x, int, int) : tiles(x) {}
+    __device__ __forceinline__ Tile at(int, int t) const { return ld_tile(tiles, t); }
+};
+// ... or, PACKED, tile i in lane i from one load per round and wave, which
+// spares a wave of many tiles the wait for a scalar load per tile, phase and
+// broadcast copy; a wave of few tiles waits longer for the one load.  Measured
+// on MI355X (us per call, a load per tile / per round, both builds alternated):
+// fp16 6.1 10^7 x K=16 reduce 353.0 / 339.4; a wave of one or two tiles, 2 10^6 x
+// K=2 fp16 reduce 7.1 / 7.5, 4 10^6 x K=2 fp32 reduce 8.3 / 9.6, x K=4 step 21.6 / 23.3.
 // A descriptor is packed into two registers (the kernel has none to spare):
 // 55 bits of start / 4 -- no address reaches further --, 8 of the count (at most
 // 128 vectors) and the tail bit.
-struct WaveTiles {
+template <int W> struct WaveTiles<W, true> {
     u2 d;
-    __device__ __forceinline__ Tile at(int i) const {
+    // tiles first, first + W, ..., below hi; at most 64 of them
+    __device__ __forceinline__ WaveTiles(const Tile* tiles, int first, int hi) {
+        const int t = first + W * static_cast<int>(threadIdx.x & 63);
+        u4 x = u4{0u, 0u, 0u, 0u};
+        if (t < hi) x = ((const FC_GLOBAL u4*)tiles)[t];
+        const uint64_t start = (static_cast<uint64_t>(x.x) | (static_cast<uint64_t>(x.y) << 32)) >> 2;
+        d.x = static_cast<uint32_t>(start);
+        d.y = (static_cast<uint32_t>(start >> 32) & 0x7fffffu) | x.z << 23 | (x.w & TAIL_BIT);
+    }
+    __device__ __forceinline__ Tile at(int i, int) const {
         const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(d.x, i));
         const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(d.y, i));
         Tile t;
@@ -593,17 +607,6 @@ struct WaveTiles {
         return t;
     }
 };
-// tiles first, first + W, ..., below hi; at most 64 of them
-template <int W> __device__ __forceinline__ WaveTiles wave_tiles(const Tile* tiles, int first, int hi) {
-    const int t = first + W * static_cast<int>(threadIdx.x & 63);
-    u4 x = u4{0u, 0u, 0u, 0u};
-    if (t < hi) x = ((const FC_GLOBAL u4*)tiles)[t];
-    const uint64_t start = (static_cast<uint64_t>(x.x) | (static_cast<uint64_t>(x.y) << 32)) >> 2;
-    WaveTiles own;
-    own.d.x = static_cast<uint32_t>(start);
-    own.d.y = (static_cast<uint32_t>(start >> 32) & 0x7fffffu) | x.z << 23 | (x.w & TAIL_BIT);
-    return own;
-}
 
 // The broadcast phase of the resident kernels: the values of the block's
 // next n tiles sit in their LDS slots (tile j in slot j, parked there by wave
@@ -615,19 +618,19 @@ template <int W> __device__ __forceinline__ WaveTiles wave_tiles(const Tile* til
 // it reads back only what it wrote itself.  Before its slots, each wave calls
 // extra(d) with the destination, to store values it holds in registers.
 // Every wave of the block calls it.
-template <int W, int U, class Extra>
-__device__ __forceinline__ void store_slots(const WaveTiles& own, int first, float* const* dst, int K,
-                                            const float* slots, int n, Extra&& extra) {
+template <int W, int U, bool PACKED, class Extra>
+__device__ __forceinline__ void store_slots(const WaveTiles<W, PACKED>& own, int first, int lo, float* const* dst,
+                                            int K, const float* slots, int n, Extra&& extra) {
     constexpr int SLOT = RESIDENT_SLOT * U;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint32_t lane = threadIdx.x & 63;
     gptr_w_t next = gwrite(ldc(dst, 0));
     for (int k = 0; k < K; ++k) {
-        const gptr_w_t d = next;
-        next = gwrite(ldc(dst, k + 1));  // the table is padded past the last one
+        const gptr_w_t d = PACKED ? next : gwrite(ldc(dst, k));
+        if (PACKED) next = gwrite(ldc(dst, k + 1));  // the table is padded past the last one
         extra(d);
         for (int j = q, i = first; j < n; j += W, ++i) {
-            const Tile tile = own.at(i);
+            const Tile tile = own.at(i, lo + j);
             const float* slot = slots + j * SLOT;
             const uint64_t start4 = tile.start * 4;
             if (!(tile.seg & TAIL_BIT)) {
@@ -768,6 +771,7 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
     const ReduceArgs& a = ra.r;
     constexpr int SLOT = RESIDENT_SLOT * U;  // floats of LDS per tile of 64 * U vectors
     constexpr int NKEEP = RT > 0 ? RT : 1;
+    constexpr bool PACKED = RT > 0;  // such a plan's waves have ten tiles and more
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint32_t lane = threadIdx.x & 63;
     for (int round = 0; round < ra.rounds; ++round) {
@@ -776,18 +780,18 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
         const int lo = ldc(ra.ranges, b);
         const int hi = ldc(ra.ranges, b + 1);
         const int lo_lds = lo + W * RT;  // tile lo_lds + j sits in LDS slot j
-        const WaveTiles own = wave_tiles<W>(a.tiles, lo + q, hi);
+        const WaveTiles<W, PACKED> own(a.tiles, lo + q, hi);
         // phase 1: tiles lo + q + W i with i < RT into registers (the loop is
         // unrolled, so that kept[] is indexed by constants) ...
         Acc<U, 4> kept[NKEEP];
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
             const int t = lo + q + W * i;
-            if (t < hi) reduce_tile<DT, U, C, MAXD, TREE>(a, own.at(i), lane, kept[i]);
+            if (t < hi) reduce_tile<DT, U, C, MAXD, TREE>(a, own.at(i, t), lane, kept[i]);
         }
         // ... the others into LDS, in element order
         for (int t = lo_lds + q, i = RT; t < hi; t += W, ++i) {
-            const Tile tile = own.at(i);
+            const Tile tile = own.at(i, t);
             float* slot = slots + (t - lo_lds) * SLOT;
             Acc<U, 4> x;
             reduce_tile<DT, U, C, MAXD, TREE>(a, tile, lane, x);
@@ -809,10 +813,10 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
                     for (int i = 0; i < 4; ++i) slot[(lane + 64 * u) * 4 + i] = x.a[u][i];
             }
         }
-        // the rates of the wave's tiles, like their descriptors one per lane,
-        // asked for while the block's other waves end phase 1
+        // PACKED: the rates of the wave's tiles, like their descriptors one per
+        // lane, asked for while the block's other waves end phase 1
         f2 rates = f2{0.0f, 0.0f};
-        if constexpr (MODE == MODE_STEP) {
+        if constexpr (MODE == MODE_STEP && PACKED) {
             const int t = lo + q + W * static_cast<int>(lane);
             const uint32_t seg = t < hi ? ((const FC_GLOBAL Tile*)a.tiles)[t].seg & SEG_MASK : 0u;
             rates = ((const FC_GLOBAL f2*)a.mults)[seg];
@@ -832,23 +836,39 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
             c[2] = static_cast<unsigned long long>(__builtin_amdgcn_s_getreg((3 << 11) | 20));
         }
         // phase 2: the register-held tiles ...
-        auto rate = [](float x, int i) {
+        auto lane_of = [](float x, int i) {
             return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i));
         };
-        auto finish_reg = [&](int i, Acc<U, 4>& x) {
-            const Tile tile = own.at(i);
-            const float lr_j = rate(rates.x, i), wd_j = rate(rates.y, i);
+        auto rates_of = [&](const Tile& tile, int i) {
+            f2 r = f2{0.0f, 0.0f};
+            if constexpr (MODE == MODE_STEP) {
+                if constexpr (PACKED) {
+                    r.x = lane_of(rates.x, i);
+                    r.y = lane_of(rates.y, i);
+                } else {
+                    const int sj = static_cast<int>(tile.seg & SEG_MASK);
+                    r.x = a.lr * ldc(a.mults, 2 * sj);
+                    r.y = a.wd * ldc(a.mults, 2 * sj + 1);
+                }
+            }
+            return r;
+        };
+        auto finish_reg = [&](int i, int t, Acc<U, 4>& x) {
+            const Tile tile = own.at(i, t);
+            const f2 r = rates_of(tile, i);
+            const float lr_j = r.x, wd_j = r.y;
             finish_kept<DT, U, MODE>(a, tile, lane, lr_j, wd_j, x);  // leaves w' in x
         };
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
             const int t = lo + q + W * i;
-            if (t < hi) finish_reg(i, kept[i]);
+            if (t < hi) finish_reg(i, t, kept[i]);
         }
         // ... then those in LDS
         for (int j = q, i = RT; j < hi - lo_lds; j += W, ++i) {
-            const Tile tile = own.at(i);
-            const float lr_j = rate(rates.x, i), wd_j = rate(rates.y, i);
+            const Tile tile = own.at(i, lo_lds + j);
+            const f2 r = rates_of(tile, i);
+            const float lr_j = r.x, wd_j = r.y;
             float* slot = slots + j * SLOT;
             const uint64_t start4 = tile.start * 4;
             if (!(tile.seg & TAIL_BIT)) {
@@ -870,10 +890,10 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
 #pragma unroll
                 for (int i = 0; i < RT; ++i) {
                     const int t = lo + q + W * i;
-                    if (t < hi) store_kept<DT, U, CPOL_RESIDENT_STORE>(gwrite(a.v), own.at(i), lane, kept[i]);
+                    if (t < hi) store_kept<DT, U, CPOL_RESIDENT_STORE>(gwrite(a.v), own.at(i, t), lane, kept[i]);
                 }
                 for (int j = q, i = RT; j < hi - lo_lds; j += W, ++i) {
-                    const Tile tile = own.at(i);
+                    const Tile tile = own.at(i, lo_lds + j);
                     const float* slot = slots + j * SLOT;
                     const uint64_t start4 = tile.start * 4;
                     if (!(tile.seg & TAIL_BIT)) {
@@ -891,14 +911,14 @@ __global__ __launch_bounds__(64 * W) void resident_kernel(ResidentArgs ra) {
         }
         if constexpr (MODE == MODE_STEP) {
             // phase 3, the broadcast: w' now sits in the registers and slots
-            if (a.dst)
-                store_slots<W, U>(own, RT, a.dst, a.K, slots, hi - lo_lds, [&](gptr_w_t d) {
+            auto store_regs = [&](gptr_w_t d) {
 #pragma unroll
-                    for (int i = 0; i < RT; ++i) {
-                        const int t = lo + q + W * i;
-                        if (t < hi) store_kept<DT, U>(d, own.at(i), lane, kept[i]);
-                    }
-                });
+                for (int i = 0; i < RT; ++i) {
+                    const int t = lo + q + W * i;
+                    if (t < hi) store_kept<DT, U>(d, own.at(i, t), lane, kept[i]);
+                }
+            };
+            if (a.dst) store_slots<W, U>(own, RT, lo_lds, a.dst, a.K, slots, hi - lo_lds, store_regs);
         }
         __syncthreads();  // the next round's phase 1 overwrites the slots
     }
@@ -978,7 +998,7 @@ __global__ __launch_bounds__(256) void bcast_kernel(BcastArgs a) {
 // a piece into LDS slots (wave q the tiles lo + q, lo + q + W, ...), and the
 // block stores them to the K destinations one destination at a time
 // (store_slots, whose last barrier frees the slots for the next piece).
-template <int W, int U>
+template <int W, int U, bool PACKED>
 __global__ __launch_bounds__(64 * W) void resident_bcast_kernel(BcastArgs a) {
     extern __shared__ f4 slot_vecs[];
     float* slots = reinterpret_cast<float*>(slot_vecs);
@@ -989,9 +1009,9 @@ __global__ __launch_bounds__(64 * W) void resident_bcast_kernel(BcastArgs a) {
     const int hi = ldc(a.ranges, blockIdx.x + 1);
     for (int p0 = lo; p0 < hi; p0 += a.slots) {
         const int p1 = hi - p0 < a.slots ? hi : p0 + a.slots;
-        const WaveTiles own = wave_tiles<W>(a.tiles, p0 + q, p1);
+        const WaveTiles<W, PACKED> own(a.tiles, p0 + q, p1);
         for (int t = p0 + q, i = 0; t < p1; t += W, ++i) {
-            const Tile tile = own.at(i);
+            const Tile tile = own.at(i, t);
             float* slot = slots + (t - p0) * SLOT;
             const uint64_t start4 = tile.start * 4;
             if (!(tile.seg & TAIL_BIT)) {
@@ -1004,7 +1024,7 @@ __global__ __launch_bounds__(64 * W) void resident_bcast_kernel(BcastArgs a) {
                 ld32s<1>(gread(a.src) + start4, lane * 4, slot + lane);
             }
         }
-        store_slots<W, U>(own, 0, a.dst, a.K, slots, p1 - p0, [](gptr_w_t) {});
+        store_slots<W, U>(own, 0, p0, a.dst, a.K, slots, p1 - p0, [](gptr_w_t) {});
     }
 }
 

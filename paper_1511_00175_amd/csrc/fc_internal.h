@@ -118,7 +118,8 @@ hipError_t prepare_chain_f16(size_t lds);
 hipError_t launch_split_f16(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s);
 hipError_t launch_bcast(const Shape& sh, int grid, int groups, uint64_t n_elems, BcastArgs a, hipStream_t s);
-hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, const BcastArgs& a, hipStream_t s);
+hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, bool packed, const BcastArgs& a,
+                                 hipStream_t s);
 hipError_t prepare_resident_bcast(const Shape& sh, size_t lds);
 hipError_t prepare_resident_f32(const Shape& sh, size_t lds);
 hipError_t prepare_resident_f16(const Shape& sh, size_t lds);

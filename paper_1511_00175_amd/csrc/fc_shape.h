@@ -251,6 +251,13 @@ inline bool default_resident(int K, int bytes_per_element, int64_t rounds, uint6
 inline bool one_pass_f16(int K, uint64_t n_elems) { return K <= (n_elems <= (uint64_t(1) << 23) ? 16 : 8); }
 constexpr int ONE_PASS_BCAST_K = 4;
 
+// fc_broadcast on a resident plan packs the tiles' descriptors into registers
+// for its passes over the block's slots where a wave has more than two tiles
+// (measured on MI355X, us, a load per tile / packed, destinations not in the
+// Infinity Cache: fp16 plans 1.4 10^7 x K=4 58.2 / 52.0; a wave of one tile,
+// packed slower: 4 10^5 x K=8 4.0 / 4.3).
+inline bool bcast_packed(int K, int64_t ntiles, int64_t ranges) { return K >= 4 && ntiles > 2 * RESIDENT_WAVES * ranges; }
+
 // Resident launches record each block's rate (for fc_plan_balance) when a
 // block's share of a round is at least this many tiles.  Measured on
 // MI355X: the record costs about 0.6 us per launch (the timer read and the

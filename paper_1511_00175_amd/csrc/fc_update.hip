@@ -73,15 +73,17 @@ hipError_t launch_bcast(const Shape& sh, int grid, int groups, uint64_t n_elems,
 
 // The resident broadcast for a plan's resident tile shape (1 or 2 lane
 // vectors); `lds` is the plan's LDS per block.
-template <class F> hipError_t pick_resident_bcast(const Shape& sh, F&& f) {
+template <class F> hipError_t pick_resident_bcast(const Shape& sh, bool packed, F&& f) {
     if (sh.block != 64) return hipErrorInvalidValue;
-    if (sh.vecs == 1) return f(&resident_bcast_kernel<RESIDENT_WAVES, 1>);
-    if (sh.vecs == 2) return f(&resident_bcast_kernel<RESIDENT_WAVES, 2>);
+    constexpr int W = RESIDENT_WAVES;
+    if (sh.vecs == 1) return packed ? f(&resident_bcast_kernel<W, 1, true>) : f(&resident_bcast_kernel<W, 1, false>);
+    if (sh.vecs == 2) return packed ? f(&resident_bcast_kernel<W, 2, true>) : f(&resident_bcast_kernel<W, 2, false>);
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, const BcastArgs& a, hipStream_t s) {
-    return pick_resident_bcast(sh, [&](auto kernel) {
+hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, bool packed, const BcastArgs& a,
+                                 hipStream_t s) {
+    return pick_resident_bcast(sh, packed, [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * RESIDENT_WAVES), lds, s, a);
         return hipGetLastError();
     });
@@ -90,10 +92,14 @@ hipError_t launch_resident_bcast(const Shape& sh, int grid, size_t lds, const Bc
 // Allow up to `lds` bytes of dynamic LDS for the kernel (a property of the
 // kernel, set when a resident plan is created, like the step kernels').
 hipError_t prepare_resident_bcast(const Shape& sh, size_t lds) {
-    return pick_resident_bcast(sh, [&](auto kernel) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   static_cast<int>(lds));
-    });
+    for (bool packed : {false, true}) {
+        const hipError_t e = pick_resident_bcast(sh, packed, [&](auto kernel) {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Read probe: a plain streaming read of one contiguous buffer, the ceiling a

@@ -53,3 +53,22 @@ def test_broadcast_stores_do_not_wait(tmp_path):
     assert len(seen) >= 5
     paced = [name for name, loops in seen if "bcast_kernelILi4ELi1ELi1E" in name]
     assert {name: loops for name, loops in seen if loops and name not in paced} == {}
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+@pytest.mark.parametrize("src", ["fc_reduce_f32.hip", "fc_reduce_f16.hip"])
+def test_resident_tiles_of_few_read_descriptors_one_by_one(tmp_path, src):
+    """Resident kernels without register-held tiles serve plans whose waves may
+    have one tile: they read a tile's descriptor with a scalar load, not with a
+    vector load for the round, whose longer wait comes before the first
+    replica (replicas, w and v are read with buffer loads)."""
+    asm = tmp_path / "out.s"
+    cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-ffp-contract=off",
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", f"-I{os.path.join(ROOT, 'include')}",
+           f"-I{CSRC}", "--cuda-device-only", "-S", "-o", str(asm), os.path.join(CSRC, src)]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr
+    few = [(name, [x for x in body if "global_load_dwordx4" in x]) for name, body in kernels(asm.read_text())
+           if "resident_kernel" in name and name.split("EEEv")[0].endswith("ELi0")]
+    assert len(few) >= 12
+    assert {name: loads for name, loads in few if loads} == {}
