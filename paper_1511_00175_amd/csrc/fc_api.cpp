@@ -40,7 +40,7 @@ struct fc_plan {
     float* d_sum = nullptr;          // raw-sum scratch of the two-pass schedule (extent floats)
     int schedule = FC_SCHED_FUSED;   // resolved schedule of fc_step
     int* d_ranges = nullptr;         // RESIDENT: tile range of each block in each round (res_grid * res_rounds + 1)
-    bool capped = false;             // the caller limits the grid (max_blocks)
+    int cap = 0;                     // the caller's max_blocks, or 0
     int res_grid = 0;
     int res_rounds = 0;
     bool res_one_launch = false;     // every round in one launch (FC_SCHED_RESIDENT_ONE_LAUNCH)
@@ -423,15 +423,29 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     const uint64_t per_elem = static_cast<uint64_t>(K) * (gdt == FC_F16 ? 2 : 4) + 16;
     const uint64_t step_bytes = n_elems > UINT64_MAX / per_elem ? UINT64_MAX : n_elems * per_elem;
     const bool choose = sched_req == FC_SCHED_AUTO && !shape_given;
+    // The shapes and kernels made for short plans spread the work over more,
+    // smaller blocks; a grid that the caller caps below them keeps the larger
+    // tiles.  Measured on MI355X, us, larger tiles / short plans' ones: 300000 x K=2
+    // fp16 reduce in 8 blocks 15.8 / 148, 65536 x K=17 fp16 linear step in 1 block 78 /
+    // 628, 4194304 x K=4 fp16 reduce in 128 blocks 22.5 / 142.
+    const uint64_t cap_blocks = opts && opts->max_blocks > 0 ? static_cast<uint64_t>(opts->max_blocks) : UINT64_MAX;
     // tiles of 256, 128 and 64 elements: is the plan too short to fill the
     // chip with one wave per tile?
-    const bool split = choose && fc::default_split(gdt, order == FC_ORDER_TREE, K, std::max(1, cus), lds_cu, tiles_of(64),
-                                                   tiles_of(32), tiles_of(16), sh);
+    const uint64_t tiles256 = tiles_of(64), tiles128 = tiles_of(32), tiles64 = tiles_of(16);
+    fc::Shape few = sh;
+    const bool split = choose &&
+                       fc::default_split(gdt, order == FC_ORDER_TREE, K, std::max(1, cus), lds_cu, tiles256, tiles128,
+                                         tiles64, few) &&
+                       (few.lane == 2 ? tiles128 : tiles64) <= cap_blocks;
+    if (split) sh = few;
     const bool resident = res_req || (choose && !split &&
                                       fc::default_resident(K, gdt == FC_F16 ? 2 : 4, static_cast<int64_t>(res_rounds),
                                                            n_elems, step_bytes));
-    if (choose && !split && !resident && step_bytes < fc::RESIDENT_MIN_BYTES)
-        fc::short_shape(gdt, K, tiles_of(64), sh);
+    if (choose && !split && !resident && step_bytes < fc::RESIDENT_MIN_BYTES) {
+        few = sh;
+        fc::short_shape(gdt, K, tiles256, few);
+        if (tiles_of(static_cast<uint64_t>(few.block) * few.vecs) <= cap_blocks) sh = few;
+    }
     if (resident) {
         sh.block = 64;
         sh.vecs = res_u;
@@ -499,8 +513,10 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     }
     p->ntiles = static_cast<int>(tiles.size());
     int grid = p->ntiles;
-    p->capped = opts && opts->max_blocks > 0;
-    if (p->capped) grid = std::min(grid, opts->max_blocks);
+    if (opts && opts->max_blocks > 0) {
+        p->cap = opts->max_blocks;
+        grid = std::min(grid, p->cap);
+    }
     p->grid = grid;
 
     // fc_step schedule (see fc_schedule)
@@ -512,7 +528,8 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
         p->res_grid = res_grid;
         p->res_rounds = static_cast<int>(res_rounds);
         p->res_one_launch = sched_req == FC_SCHED_RESIDENT_ONE_LAUNCH;
-        p->res_one_pass = !res_req && gdt == FC_F16 && res_rounds == 1 && fc::one_pass_f16(K, n_elems);
+        p->res_one_pass = !res_req && gdt == FC_F16 && res_rounds == 1 && fc::one_pass_f16(K, n_elems) &&
+                          res_tiles <= cap_blocks;
         p->res_lds = static_cast<int>(res_lds);
         p->res_slot = static_cast<int>(slot_bytes);
         p->res_in_regs = static_cast<int>(in_regs);
@@ -787,8 +804,8 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
         rc = launch(p, FC_KERNEL_BCAST, s, true, [&] {
             if (p->schedule != FC_SCHED_RESIDENT)
                 return fc::launch_bcast(p->shape, p->grid,
-                                        fc::bcast_groups(p->shape, p->K, p->grid, p->n_elems, p->capped), p->n_elems,
-                                        a, s);
+                                        fc::bcast_groups(p->shape, p->K, p->grid, p->n_elems, p->cap), p->n_elems, a,
+                                        s);
             // resident plans: the step's ranges, one launch per round, or
             // all rounds' ranges in one launch of grid x rounds blocks
             // (block b takes range b of the whole table)

@@ -187,12 +187,14 @@ inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, int lds_cu, u
 // 14.7 | 21.3 / 25.3, 600000 x K=64 19.9 / 20.4 | 28.9 / 37.8, 10^6 x K=16 9.3 /
 // 9.3 | 14.6 / 16.7; one-wave blocks 100000 x K=200 (391) 11.7 / 11.7 | 12.3 /
 // 14.5.
-// A grid that the caller capped stays as it is: the cap holds for every launch.
+// A caller's cap on the grid (0: none) holds for every launch.
 constexpr int BCAST_WAVES = 4096, BCAST_SHARE_WAVES = 256;
-inline int bcast_groups(const Shape& sh, int K, int grid, uint64_t n_elems, bool capped) {
+inline int bcast_groups(const Shape& sh, int K, int grid, uint64_t n_elems, int cap) {
     const int64_t waves = std::max<int64_t>(1, sh.lane ? grid : static_cast<int64_t>(grid) * (sh.block / 64));
-    if (capped || n_elems > (uint64_t(1) << 18) || (!sh.lane && waves > BCAST_SHARE_WAVES)) return 1;
-    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((K + 7) / 8, (BCAST_WAVES + waves - 1) / waves)));
+    if (n_elems > (uint64_t(1) << 18) || (!sh.lane && waves > BCAST_SHARE_WAVES)) return 1;
+    int64_t groups = std::min<int64_t>((K + 7) / 8, (BCAST_WAVES + waves - 1) / waves);
+    if (cap > 0) groups = std::min<int64_t>(groups, cap / std::max(1, grid));
+    return static_cast<int>(std::max<int64_t>(1, groups));
 }
 
 inline bool compiled_pair(int u, int c) {

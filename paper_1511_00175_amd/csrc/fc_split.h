@@ -5,8 +5,8 @@
 // With one wave per tile (reduce_kernel) a plan of few tiles leaves most of
 // the chip idle, and each wave works through its K replicas batch after batch,
 // one trip to memory each: time goes with K / batch, not with the bytes.
-// Here a tile is 64 lanes of V = 1, 2 or 4 elements and its block has up to
-// 16 waves, so that every replica byte of a step of a few tens of MB is asked
+// Here a tile is 64 lanes of V = 1 or 2 elements and its block has up to 16
+// waves, so that every replica byte of a step of a few tens of MB is asked
 // for at once, from every compute unit.
 //
 // Tree order: wave q reduces replicas [q run, (q + 1) run) in registers, run a
@@ -257,20 +257,15 @@ template <int DT, int V, bool TREE, int MODE>
 __global__ __launch_bounds__(64 * SPLIT_WAVES) void split_kernel(ReduceArgs a, int run) {
     extern __shared__ f4 slot_vecs[];
     float* lds = reinterpret_cast<float*>(slot_vecs);
-    for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-        const Tile tile = ld_tile(a.tiles, t);
-        float lr_j = 0.0f, wd_j = 0.0f;
-        if constexpr (MODE == MODE_STEP) {
-            const int j = static_cast<int>(tile.seg & SEG_MASK);
-            lr_j = a.lr * ldc(a.mults, 2 * j);
-            wd_j = a.wd * ldc(a.mults, 2 * j + 1);
-        }
-        if (!(tile.seg & TAIL_BIT))
-            split_tile<DT, V, TREE, MODE>(a, run, lds, tile.start, tile.count * 4, lr_j, wd_j);
-        else
-            split_tile<DT, 1, TREE, MODE>(a, run, lds, tile.start, tile.count, lr_j, wd_j);
-        __syncthreads();  // the next tile overwrites the LDS
+    const Tile tile = ld_tile(a.tiles, blockIdx.x);
+    float lr_j = 0.0f, wd_j = 0.0f;
+    if constexpr (MODE == MODE_STEP) {
+        const int j = static_cast<int>(tile.seg & SEG_MASK);
+        lr_j = a.lr * ldc(a.mults, 2 * j);
+        wd_j = a.wd * ldc(a.mults, 2 * j + 1);
     }
+    if (!(tile.seg & TAIL_BIT)) split_tile<DT, V, TREE, MODE>(a, run, lds, tile.start, tile.count * 4, lr_j, wd_j);
+    else split_tile<DT, 1, TREE, MODE>(a, run, lds, tile.start, tile.count, lr_j, wd_j);
 }
 
 // Linear order where a tile has a compute unit to itself: the additions' serial
@@ -293,60 +288,57 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void chain_kernel(ReduceArgs a) {
     const int per = (nw - 1) * SPLIT_C;  // replicas per buffer
     const int row = (q - 1) * SPLIT_C;   // of a loading wave
     const uint32_t lane = threadIdx.x & 63;
-    for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-        const Tile tile = ld_tile(a.tiles, t);
-        const uint32_t ne = tile.seg & TAIL_BIT ? tile.count : tile.count * 4;
-        const uint64_t start4 = tile.start * 4;
-        const bool own = lane < ne;
-        const uint32_t e = own ? lane : 0u;
-        float lr_j = 0.0f, wd_j = 0.0f, w = 0.0f, v = 0.0f;
-        typename Rep<DT, 1>::raw r[SPLIT_C];
+    const Tile tile = ld_tile(a.tiles, blockIdx.x);
+    const uint32_t ne = tile.seg & TAIL_BIT ? tile.count : tile.count * 4;
+    const uint64_t start4 = tile.start * 4;
+    const bool own = lane < ne;
+    const uint32_t e = own ? lane : 0u;
+    float lr_j = 0.0f, wd_j = 0.0f, w = 0.0f, v = 0.0f;
+    typename Rep<DT, 1>::raw r[SPLIT_C];
+    if (q) {
+        load_batch<DT, 1>(a.grads, row, a.K - row, tile.start * SG, e * SG, r);
+    } else if constexpr (MODE == MODE_STEP) {
+        const int j = static_cast<int>(tile.seg & SEG_MASK);
+        lr_j = a.lr * ldc(a.mults, 2 * j);
+        wd_j = a.wd * ldc(a.mults, 2 * j + 1);
+        ld32s<1>(gread(a.w) + start4, e * 4, &w);
+        ld32s<1>(gread(a.v) + start4, e * 4, &v);
+    }
+    float s = -0.0f;  // -0 + x is x, whatever x
+    float* buf = lds;
+    for (int c0 = 0; c0 < a.K; c0 += per) {
         if (q) {
-            load_batch<DT, 1>(a.grads, row, a.K - row, tile.start * SG, e * SG, r);
-        } else if constexpr (MODE == MODE_STEP) {
-            const int j = static_cast<int>(tile.seg & SEG_MASK);
-            lr_j = a.lr * ldc(a.mults, 2 * j);
-            wd_j = a.wd * ldc(a.mults, 2 * j + 1);
-            ld32s<1>(gread(a.w) + start4, e * 4, &w);
-            ld32s<1>(gread(a.v) + start4, e * 4, &v);
-        }
-        float s = -0.0f;  // -0 + x is x, whatever x
-        float* buf = lds;
-        for (int c0 = 0; c0 < a.K; c0 += per) {
-            if (q) {
 #pragma unroll
-                for (int j = 0; j < SPLIT_C; ++j) Rep<DT, 1>::widen(r[j], &buf[(row + j) * T + lane]);
-                const int k1 = c0 + per + row;
-                load_batch<DT, 1>(a.grads, k1, a.K - k1, tile.start * SG, e * SG, r);
-            }
-            // wave 0 added the buffer that is filled next before it came here
+            for (int j = 0; j < SPLIT_C; ++j) Rep<DT, 1>::widen(r[j], &buf[(row + j) * T + lane]);
+            const int k1 = c0 + per + row;
+            load_batch<DT, 1>(a.grads, k1, a.K - k1, tile.start * SG, e * SG, r);
+        }
+        // wave 0 added the buffer that is filled next before it came here
+        __syncthreads();
+        if (!q) s = chain<T, SPLIT_C>(buf + lane, a.K - c0 < per ? a.K - c0 : per, s);
+        buf = buf == lds ? lds + per * T : lds;
+    }
+    if constexpr (MODE == MODE_REDUCE) {
+        if (!q && own) st32r<1>(gwrite(a.out) + start4, e * 4, &s);
+    } else {
+        float wn, vn;
+        sgd1(s, w, v, lr_j, a.mu, wd_j, a.c, wn, vn);
+        if (!q && own) {
+            st32r<1>(gwrite(a.w) + start4, e * 4, &wn);
+            st32r<1>(gwrite(a.v) + start4, e * 4, &vn);
+            if (a.out) st32r<1>(gwrite(a.out) + start4, e * 4, &s);
+        }
+        if (a.dst) {
+            __syncthreads();  // buffers done with
+            if (!q) lds[lane] = wn;
             __syncthreads();
-            if (!q) s = chain<T, SPLIT_C>(buf + lane, a.K - c0 < per ? a.K - c0 : per, s);
-            buf = buf == lds ? lds + per * T : lds;
-        }
-        if constexpr (MODE == MODE_REDUCE) {
-            if (!q && own) st32r<1>(gwrite(a.out) + start4, e * 4, &s);
-        } else {
-            float wn, vn;
-            sgd1(s, w, v, lr_j, a.mu, wd_j, a.c, wn, vn);
-            if (!q && own) {
-                st32r<1>(gwrite(a.w) + start4, e * 4, &wn);
-                st32r<1>(gwrite(a.v) + start4, e * 4, &vn);
-                if (a.out) st32r<1>(gwrite(a.out) + start4, e * 4, &s);
-            }
-            if (a.dst) {
-                __syncthreads();  // buffers done with
-                if (!q) lds[lane] = wn;
-                __syncthreads();
-                const int n = (a.K + nw - 1) / nw, k0 = q * n;  // the wave's destinations
-                if (own) {
-                    float x = lds[lane];
-                    settle<1>(&x);
-                    st32_copies_shared<1>(a.dst, k0, k0 + n < a.K ? k0 + n : a.K, start4, e * 4, &x);
-                }
+            const int n = (a.K + nw - 1) / nw, k0 = q * n;  // the wave's destinations
+            if (own) {
+                float x = lds[lane];
+                settle<1>(&x);
+                st32_copies_shared<1>(a.dst, k0, k0 + n < a.K ? k0 + n : a.K, start4, e * 4, &x);
             }
         }
-        __syncthreads();  // the next tile overwrites the LDS
     }
 }
 

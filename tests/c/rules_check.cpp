@@ -33,16 +33,19 @@ static void copies() {
         for (uint64_t n : {1000ull, 65536ull, 131072ull, 262144ull, 300000ull, 600000ull, 1000000ull, 3000000ull})
             for (const fc::Shape& sh : {u4, one, split}) {
                 const int grid = tiles(n, sh.lane ? 64 * sh.lane : sh.block * sh.vecs * 4);
-                const int g = fc::bcast_groups(sh, K, grid, n, false);
+                const int g = fc::bcast_groups(sh, K, grid, n, 0);
                 CHECK(g >= 1 && g <= (K + 7) / 8, "K=%d n=%llu: %d", K, (unsigned long long)n, g);
                 // a caller's cap holds, also where it is wider than the grid
-                CHECK(fc::bcast_groups(sh, K, grid, n, true) == 1, "capped K=%d", K);
+                for (int cap : {grid, grid + 1, 3 * grid, 100 * grid}) {
+                    const int c = fc::bcast_groups(sh, K, grid, n, cap);
+                    CHECK(c >= 1 && c <= g && c * grid <= cap, "K=%d cap %d: %d x %d", K, cap, c, grid);
+                }
                 // writes bound the copies of larger plans
                 CHECK(n <= 262144 || g == 1, "K=%d n=%llu: %d", K, (unsigned long long)n, g);
             }
-    CHECK(fc::bcast_groups(one, 1000, tiles(4000, 256), 4000, false) == 125, "4000 x K=1000");
-    CHECK(fc::bcast_groups(u4, 64, tiles(262144, 4096), 262144, false) == 8, "262144 x K=64");
-    CHECK(fc::bcast_groups(one, 200, tiles(100000, 256), 100000, false) == 1, "100000 x K=200");
+    CHECK(fc::bcast_groups(one, 1000, tiles(4000, 256), 4000, 0) == 125, "4000 x K=1000");
+    CHECK(fc::bcast_groups(u4, 64, tiles(262144, 4096), 262144, 0) == 8, "262144 x K=64");
+    CHECK(fc::bcast_groups(one, 200, tiles(100000, 256), 100000, 0) == 1, "100000 x K=200");
 }
 
 int main(int, char** argv) {
