@@ -812,7 +812,7 @@ static int fc_broadcast_body(fc_plan* p, const float* src, float* const* dst, vo
             a.slots = p->res_lds / p->res_slot;
             const int per_launch = p->res_one_launch ? p->res_rounds : 1;
             const bool packed =
-                fc::bcast_packed(p->K, p->ntiles, static_cast<int64_t>(p->res_grid) * p->res_rounds);
+                fc::bcast_packed(p->K, p->ntiles, static_cast<int64_t>(p->res_grid) * p->res_rounds, p->cap);
             for (int round = 0; round < p->res_rounds; round += per_launch) {
                 a.ranges = p->d_ranges + static_cast<size_t>(round) * p->res_grid;
                 const hipError_t e = fc::launch_resident_bcast(p->shape, p->res_grid * per_launch,

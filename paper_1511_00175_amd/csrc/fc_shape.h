@@ -257,8 +257,12 @@ constexpr int ONE_PASS_BCAST_K = 4;
 // for its passes over the block's slots where a wave has more than two tiles
 // (measured on MI355X, us, a load per tile / packed, destinations not in the
 // Infinity Cache: fp16 plans 1.4 10^7 x K=4 58.2 / 52.0; a wave of one tile,
-// packed slower: 4 10^5 x K=8 4.0 / 4.3).
-inline bool bcast_packed(int K, int64_t ntiles, int64_t ranges) { return K >= 4 && ntiles > 2 * RESIDENT_WAVES * ranges; }
+// packed slower: 4 10^5 x K=8 4.0 / 4.3).  Where the caller caps the grid, the
+// blocks' own store rate is the bound and packing costs 5% (2^20 x K=128 in 64
+// blocks 113.4 / 119.2).
+inline bool bcast_packed(int K, int64_t ntiles, int64_t ranges, int cap) {
+    return !cap && K >= 4 && ntiles > 2 * RESIDENT_WAVES * ranges;
+}
 
 // Resident launches record each block's rate (for fc_plan_balance) when a
 // block's share of a round is at least this many tiles.  Measured on

@@ -48,11 +48,19 @@ static void copies() {
     CHECK(fc::bcast_groups(one, 200, tiles(100000, 256), 100000, 0) == 1, "100000 x K=200");
 }
 
+// resident broadcasts that pack their tiles' descriptors
+static void packed() {
+    CHECK(fc::bcast_packed(8, 214 * 256, 256, 0), "213 tiles a block");
+    CHECK(!fc::bcast_packed(8, 32 * 256, 256, 0) && fc::bcast_packed(8, 32 * 256 + 1, 256, 0), "two tiles a wave");
+    CHECK(!fc::bcast_packed(3, 214 * 256, 256, 0), "few destinations");
+    CHECK(!fc::bcast_packed(128, 4096, 64, 64), "capped grid");
+}
+
 int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}};
+    } rules[] = {{"copies", copies}, {"packed", packed}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();
