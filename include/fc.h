@@ -161,8 +161,8 @@ typedef enum {
  * at least 1024 tiles of 256 elements, (4, 4, 256) for fp16 with K <= 4 and at least
  * 4096 such tiles, else (1, 16, 64); otherwise (also with an explicit schedule
  * or shape field) fp16 -> (4 vectors, 4 replicas, 256
- * threads); fp32 with K <= 2 -> (1, 8, 256); fp32 with 16 < K <= 64 ->
- * (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the
+ * threads); fp32 with K <= 2, or K <= 4 below 2^23 parameters or with max_blocks
+ * -> (1, 8, 256); fp32 with 16 < K <= 64 -> (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the
  * streaming (nt) hint. */
 typedef struct {
     int block_threads;   /* 64, 128 or 256 threads per block */

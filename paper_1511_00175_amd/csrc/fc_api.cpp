@@ -194,8 +194,8 @@ void note_stream(fc_plan* p, hipStream_t s) {
     p->have_last_stream = true;
 }
 
-int validate_opts(const fc_launch_opts* o, fc_dtype gdt, int K, fc::Shape& sh, bool& shape_given) {
-    fc::default_shape(gdt, K, sh);
+int validate_opts(const fc_launch_opts* o, fc_dtype gdt, int K, uint64_t n_elems, fc::Shape& sh, bool& shape_given) {
+    fc::default_shape(gdt, K, n_elems, o && o->max_blocks > 0, sh);
     shape_given = false;
     if (o) {
         // k_waves: one wave reduces all K replicas of its lane-vectors (0 or 1)
@@ -360,7 +360,7 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
     if (end > (UINT64_MAX / 8)) return FC_EINVAL;
     fc::Shape sh{};
     bool shape_given = false;
-    int rc = validate_opts(opts, gdt, K, sh, shape_given);
+    int rc = validate_opts(opts, gdt, K, n_elems, sh, shape_given);
     if (rc) return rc;
     const int sched_req = opts ? opts->schedule : FC_SCHED_AUTO;
     const bool res_req = sched_req == FC_SCHED_RESIDENT || sched_req == FC_SCHED_RESIDENT_ONE_LAUNCH;

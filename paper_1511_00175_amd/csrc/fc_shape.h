@@ -15,6 +15,7 @@ namespace fc {
 // Launch-shape defaults, measured on MI355X for the five workloads:
 //   fp16 replicas       : 4 vectors per lane, 4 replicas per batch, 256 threads
 //   fp32, K <= 2        : 1 vector per lane, 8 replicas per batch, 256 threads
+//         (K <= 4 below 2^23 parameters or with a capped grid)
 //   fp32, 16 < K <= 64  : 4 vectors per lane, 2 replicas per batch, 256 threads
 //   other fp32          : 1 vector per lane, 16 replicas per batch, 64 threads
 // Four vectors per lane make every wave read 4 KiB of one replica at a time,
@@ -23,13 +24,17 @@ namespace fc {
 // With one or two replicas a wave has little to load: 4x fewer, larger blocks
 // measured 1.3-5% faster on large plans (4 10^7 parameters, us per step, (1, 8,
 // 256) vs (1, 16, 64): K=1 126.2 vs 127.6, K=2 155.9 vs 149.1 but its reduce
-// 74.4 vs 84.8); from K=3 on one wave per block wins in every call (K=3 step
-// 185.9 vs 176.4, broadcast 276 vs 261, reduce 105.7 vs 99.3; K=4 216 vs 203,
-// 341 vs 318, 134 vs 125).  Short steps have rules of their own (short_shape).
-inline void default_shape(fc_dtype gdt, int K, fc::Shape& sh) {
+// 74.4 vs 84.8); from K=3 on one wave per block wins in every call of such
+// plans (K=3 step 185.9 vs 176.4, broadcast 276 vs 261, reduce 105.7 vs 99.3;
+// K=4 216 vs 203, 341 vs 318, 134 vs 125; equal at 1.4 10^7), but not of smaller
+// ones (8000 x K=3 step 2.9 vs 3.3, 2^20 x K=3 reduce 3.4 vs 4.1, 4 10^6 x K=3
+// 12.6 vs 13.4) nor where few blocks do all the work (65536 x K=4 reduce in 1
+// block 54 vs 268).  Short steps of default
+// plans have rules of their own (short_shape).
+inline void default_shape(fc_dtype gdt, int K, uint64_t n_elems, bool capped, fc::Shape& sh) {
     if (gdt == FC_F16) {
         sh.vecs = 4; sh.kchunk = 4; sh.block = 256;
-    } else if (K <= 2) {
+    } else if (K <= (capped || n_elems < (uint64_t(1) << 23) ? 4 : 2)) {
         sh.vecs = 1; sh.kchunk = 8; sh.block = 256;
     } else if (K > 16 && K <= 64) {
         sh.vecs = 4; sh.kchunk = 2; sh.block = 256;

@@ -56,11 +56,32 @@ static void packed() {
     CHECK(!fc::bcast_packed(128, 4096, 64, 64), "capped grid");
 }
 
+static void expect(const fc::Shape& sh, int vecs, int kchunk, int block, const char* what) {
+    CHECK(sh.vecs == vecs && sh.kchunk == kchunk && sh.block == block, "%s: (%d, %d, %d)", what, sh.vecs, sh.kchunk,
+          sh.block);
+}
+
+// shapes of plans with an explicit schedule or a capped grid
+static void shapes() {
+    for (int c = 0; c < 4; ++c)
+        for (int K = 1; K <= 1024; ++K) {
+            const uint64_t n = (uint64_t(1) << 23) - c % 2;
+            const bool capped = c >= 2, few = c > 0;
+            fc::Shape sh{};
+            fc::default_shape(FC_F16, K, n, capped, sh);
+            expect(sh, 4, 4, 256, "fp16");
+            fc::default_shape(FC_F32, K, n, capped, sh);
+            if (K <= 2 || (few && K <= 4)) expect(sh, 1, 8, 256, "few replicas");
+            else if (K > 16 && K <= 64) expect(sh, 4, 2, 256, "17 to 64 replicas");
+            else expect(sh, 1, 16, 64, "other");
+        }
+}
+
 int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}, {"packed", packed}};
+    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();
