@@ -157,9 +157,11 @@ typedef enum {
  * kchunk may name either; a step whose waves share the replicas of a tile
  * (see AUTO) -> tiles of 64 lanes x 1 or 2 elements, up to 16 waves per block,
  * batches of 16; any other
- * step of less than 64 MiB -> (1, 8, 256) for fp32 with K <= 8 or with K >= 12 and
- * at least 1024 tiles of 256 elements, (4, 4, 256) for fp16 with K <= 4 and at least
- * 4096 such tiles, else (1, 16, 64); otherwise (also with an explicit schedule
+ * step of less than 64 MiB -> (1, 8, 256) for fp32 with K <= 4, with K <= 8 where
+ * its blocks' last round fills the chip to 80% (or there is one round), and with
+ * K > 16 where there are several such rounds, and for fp16 with K <= 2; (4, 4, 256)
+ * for fp16 with K <= 4 and fewer than 16 or at least 1536 tiles of 256 elements;
+ * else (1, 16, 64); otherwise (also with an explicit schedule
  * or shape field) fp16 -> (4 vectors, 4 replicas, 256
  * threads); fp32 with K <= 2, or K <= 4 below 2^23 parameters or with max_blocks
  * -> (1, 8, 256); fp32 with 16 < K <= 64 -> (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the

@@ -443,7 +443,7 @@ int fc_plan_create_ex(fc_plan** plan, const fc_segment* segs, int nseg, int K, i
                                                            n_elems, step_bytes));
     if (choose && !split && !resident && step_bytes < fc::RESIDENT_MIN_BYTES) {
         few = sh;
-        fc::short_shape(gdt, K, tiles256, few);
+        fc::short_shape(gdt, K, std::max(1, cus), tiles256, tiles_of(256), few);
         if (tiles_of(static_cast<uint64_t>(few.block) * few.vecs) <= cap_blocks) sh = few;
     }
     if (resident) {

@@ -91,22 +91,43 @@ inline int resident_rtiles(int gdt, int u, int c, int maxd) {
 }
 
 // Default shape of a step of less than RESIDENT_MIN_BYTES that one wave per
-// tile serves (default_split says no): blocks of 256 threads and batches of 8
-// for fp32 with few replicas or (unless a second batch would be nearly empty)
-// at least 1024 tiles of 256 elements, else one wave per block and batches of
-// 16; fp16 with K <= 4 and at least 2^20
-// elements keeps the 4-vector shape.  Measured on MI355X (us per step in a HIP
-// graph, (1, 8, 256) vs (1, 16, 64)): fp32 2^18 x K=8 3.6 vs 4.1, 500000 x
-// K=16 7.9 vs 8.4, 2^20 x K=8 10.1 vs 10.5, 2^17 x K=16 4.5 vs 3.7, 347457 x
-// K=9 5.2 vs 4.7; fp16
-// 2^20 x K=7 11.8 vs 7.3, K=12 12.4 vs 9.1, 2^18 x K=16 4.3 vs 4.1.  The
-// 4-vector shapes of default_shape leave most of the chip idle here: fp32
-// 2^18 x K=32 19.3 vs 7.7, fp16 2^18 x K=16 8.3 vs 4.1, 2^20 x K=16 11.4 vs
-// 10.0; 2^20 x K=4 5.9 vs 6.3.
-inline void short_shape(fc_dtype gdt, int K, uint64_t tiles256, fc::Shape& sh) {
-    if (gdt == FC_F16 && K <= 4 && tiles256 >= 4096) {
+// tile serves (default_split says no).
+//
+// fp32: blocks of 256 threads and batches of 8 with few replicas (their one
+// batch is nearly full, and a quarter of the blocks start the sooner) or, as the
+// 4-vector shapes' successor, with more than 16; else one wave per block and
+// batches of 16.  The larger blocks take 1024 elements each, so a plan of 1.2 or
+// 3.1 of them per unit ends with most units idle: from 5 replicas on they serve
+// plans whose last round of blocks is at least 80% full, or up to one block per
+// unit.  Measured on MI355X, us, (1, 8, 256) / (1, 16, 64), data in the Infinity
+// Cache: steps 2^18 x K=8 3.6 / 4.1, 520000 x K=8 5.2 / 5.3, 2^20 x K=8 8.2 / 8.5,
+// but 300000 x K=8 with broadcast 6.1 / 5.1, 800000 x K=8 reduce 5.8 / 5.1; from 9
+// replicas on two batches take longer: 300000 x K=16 5.8 / 5.1, 347457 x K=9 5.2 /
+// 4.7, 2^18 x K=12 4.5 / 4.2.
+//
+// fp16: one wave per block and batches of 16 from 5 replicas on (2^20 x K=7 step
+// 11.8 with (1, 8, 256), 7.3 with (1, 16, 64); its 4-vector shape 11.4 against 10.0
+// at K=16).  Up to 4 replicas one wave's batch is nearly empty: the 4-vector
+// shape serves plans of less than one of its blocks (1000 x K=1 reduce 2.3, 2.6
+// with one-wave blocks) and those of more than 1536 tiles of 256 elements (800000
+// x K=2 reduce 3.1 against 3.9), and between them blocks of 256 threads with
+// batches of 8 for K <= 2 (100000 x K=1 1.3x the 4-vector shape's speed over all
+// calls, one-wave blocks 1.2x), one-wave blocks for K = 3 and 4.  From 2^20
+// elements on a step that also broadcasts would be up to 11% faster with the
+// 4-vector shape (2^20 x K=12, data not in the cache, 18.2 / 20.3); its plain
+// steps and reductions are 11 to 17% slower (11.1 / 9.9, 9.1 / 7.6), and a plan
+// has one shape for all.
+inline void short_shape(fc_dtype gdt, int K, int cus, uint64_t tiles256, uint64_t tiles1024, fc::Shape& sh) {
+    const uint64_t cu = static_cast<uint64_t>(cus);
+    const uint64_t places = (tiles1024 + cu - 1) / cu * cu;  // for blocks, over all rounds
+    const bool filled = 10 * tiles1024 >= 8 * places;
+    const bool larger = gdt == FC_F16 ? K <= 2
+                        : K <= 4      ? true
+                        : K <= 8      ? tiles1024 <= cu || filled
+                                      : K > 16 && tiles1024 >= cu && filled;
+    if (gdt == FC_F16 && K <= 4 && (tiles256 < 16 || tiles256 >= 1536)) {
         sh.vecs = 4; sh.kchunk = 4; sh.block = 256;
-    } else if (gdt == FC_F32 && (K <= 8 || (K >= 12 && tiles256 >= 1024))) {
+    } else if (larger) {
         sh.vecs = 1; sh.kchunk = 8; sh.block = 256;
     } else {
         sh.vecs = 1; sh.kchunk = 16; sh.block = 64;

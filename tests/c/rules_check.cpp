@@ -77,11 +77,37 @@ static void shapes() {
         }
 }
 
+// shapes of default plans' short steps that one wave per tile serves
+static void short_steps() {
+    auto of = [](fc_dtype t, int K, uint64_t n) {
+        fc::Shape sh{};
+        fc::short_shape(t, K, 256, (n + 255) / 256, (n + 1023) / 1024, sh);
+        return sh;
+    };
+    for (uint64_t n : {64ull, 8000ull, 262144ull, 300000ull, 520000ull, 800000ull, 1048576ull})
+        for (int K = 1; K <= 16; ++K) {
+            if (K <= 4) expect(of(FC_F32, K, n), 1, 8, 256, "fp32, one batch half empty");
+            if (K > 8) expect(of(FC_F32, K, n), 1, 16, 64, "fp32, one batch of 16");
+            if (K > 4) expect(of(FC_F16, K, n), 1, 16, 64, "fp16");
+        }
+    for (uint64_t n : {53568ull, 262144ull, 520000ull, 1048576ull, 1115480ull})
+        expect(of(FC_F32, 8, n), 1, 8, 256, "fp32 K=8, rounds filled");
+    for (uint64_t n : {300000ull, 400000ull, 800000ull}) expect(of(FC_F32, 8, n), 1, 16, 64, "fp32 K=8, last round empty");
+    for (int K = 1; K <= 4; ++K) {
+        expect(of(FC_F16, K, 1000), 4, 4, 256, "fp16, one block");
+        expect(of(FC_F16, K, 800000), 4, 4, 256, "fp16, many tiles");
+        if (K <= 2) expect(of(FC_F16, K, 100000), 1, 8, 256, "fp16 K <= 2");
+        else expect(of(FC_F16, K, 100000), 1, 16, 64, "fp16 K = 3, 4");
+    }
+    expect(of(FC_F32, 32, 300000), 1, 16, 64, "fp32 K=32, last round empty");
+    expect(of(FC_F32, 32, 460000), 1, 8, 256, "fp32 K=32, rounds filled");
+}
+
 int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}};
+    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();
