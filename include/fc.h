@@ -126,8 +126,8 @@ typedef struct fc_plan fc_plan;
  *   us with one launch per round): within one launch the blocks drift apart,
  *   so one round's writes meet the next round's replica reads.
  * AUTO (no launch-shape field given): a plan of more than 16 replicas and at
- *   most 6 tiles of 256 elements per compute unit (5 for fp16 replicas in
- *   linear order; with K <= 32 fewer than 2) runs FUSED, or TWO_PASS
+ *   most 4 tiles of 256 elements per compute unit (3 for 400 fp32 replicas and
+ *   more; in linear order 5.5, for fp16 replicas 4.5; with K <= 32 fewer than 2) runs FUSED, or TWO_PASS
  *   with both passes in one launch when a parameter's replicas take more than
  *   256 bytes (K * bytes per element): its waves share the replicas of a
  *   tile, and the sum goes from the reduction to the update through LDS, so

@@ -146,9 +146,8 @@ constexpr int CHAIN_MIN_K = 640;
 constexpr int CHAIN_LDS = 2 * (SPLIT_WAVES - 1) * 16 * 64 * 4;
 
 // The split kernel (a tile is a block's work, its waves share the replicas)
-// for plans of at most 6 tiles of 256 elements per compute unit (5 for fp16 in
-// linear order, where the one wave that adds has the most to do): one wave per
-// tile, or a resident block's share of them, leaves most of the chip idle.
+// for plans of few tiles of 256 elements per compute unit: one wave per tile, or
+// a resident block's share of them, leaves most of the chip idle.
 // With K <= 16 one wave asks for all replicas in one batch, and with K <= 32
 // it does so in two, which two tiles per unit hide: those stay with one wave
 // per tile.  Measured on MI355X (us per step in a HIP graph, before / now /
@@ -156,10 +155,15 @@ constexpr int CHAIN_LDS = 2 * (SPLIT_WAVES - 1) * 16 * 64 * 4;
 // / 2.8 / 1.2, 2^16 x K=64 39 / 5.0 / 2.5, 2^16 x K=256 20.3 / 12.0 / 9.7,
 // 2^18 x K=128 24.9 / 23.8 / 19.8; fp16 16384 x K=1000 428 / 8.3 / 4.7, 2^16 x
 // K=128 44 / 4.8 / 2.5, 2^18 x K=64 22 / 8.5 / 5.4; linear order fp32 8274 x
-// K=1000 52 / 12.6 / 4.7, fp16 2^16 x K=128 58 / 5.7 / 2.5.  From 6 tiles per
-// unit on the older kernels are as fast or faster (400000 x K=64, split /
-// one wave per tile: fp32 19.6 / 19.4, fp16 11.4 / 10.9, linear 12.6 / 10.7;
-// fp16 linear 362028 x K=100, split / resident 17.3 / 15.5).
+// K=1000 52 / 12.6 / 4.7, fp16 2^16 x K=128 58 / 5.7 / 2.5.
+// How many tiles are few (split / resident, or one wave per tile below
+// RESIDENT_MIN_BYTES; data not in the Infinity Cache): in tree order up to 4 per
+// unit, where a step that broadcasts is the first to lose (fp16 300000 x K=200
+// 76 / 69, 2^18 x K=200 64 / 66), and for fp32 from 400 replicas on up to 3 (2^18
+// x K=512 93 / 82, 196608 x K=512 62 / 71); in linear order up to 5.5 (fp32
+// 360000 x K=200 48.5 / 49.3, 393216 x K=1000 243 / 231), 4.5 for fp16, where the
+// one wave that adds has the most to do (2^18 x K=400 36 / 45, 300000 x K=64 12.0,
+// with one wave per tile 10.8).
 //
 // Tiles of 128 elements where that leaves two per unit (fp16: one, its rows
 // are half as long), else of 64.  Tree: runs of 16 replicas, one batch, while
@@ -174,8 +178,8 @@ constexpr int CHAIN_LDS = 2 * (SPLIT_WAVES - 1) * 16 * 64 * 4;
 inline bool default_split(fc_dtype gdt, bool tree, int K, int cus, int lds_cu, uint64_t tiles256, uint64_t tiles128,
                           uint64_t tiles64, fc::Shape& sh) {
     const uint64_t cu = static_cast<uint64_t>(cus);
-    const uint64_t most = !tree && gdt == FC_F16 ? 5 : 6;
-    if (K <= 16 || tiles256 > most * cu || (K <= 32 && tiles256 >= 2 * cu)) return false;
+    const uint64_t half_units = tree ? (gdt == FC_F32 && K >= 400 ? 6 : 8) : gdt == FC_F16 ? 9 : 11;
+    if (K <= 16 || 2 * tiles256 > half_units * cu || (K <= 32 && tiles256 >= 2 * cu)) return false;
     sh.lane = tiles128 >= (gdt == FC_F16 ? cu : 2 * cu) ? 2 : 1;
     const uint64_t width = sh.lane == 2 ? 2 * tiles128 : tiles64;  // the grid's width in 64-element tiles
     sh.run = 16;

@@ -103,11 +103,31 @@ static void short_steps() {
     expect(of(FC_F32, 32, 460000), 1, 8, 256, "fp32 K=32, rounds filled");
 }
 
+// the plans that the split kernel serves
+static void split_plans() {
+    auto is = [](fc_dtype t, bool tree, int K, uint64_t n) {
+        fc::Shape sh{};
+        return fc::default_split(t, tree, K, 256, 160 << 10, (n + 255) / 256, (n + 127) / 128, (n + 63) / 64, sh);
+    };
+    for (fc_dtype t : {FC_F32, FC_F16})
+        for (int K : {33, 64, 128, 200, 399, 400, 512, 1024}) {
+            const bool many = t == FC_F32 && K >= 400;
+            CHECK(is(t, true, K, 196608), "tree K=%d, 3 tiles per unit", K);
+            CHECK(is(t, true, K, 262144) == !many, "tree K=%d, 4 tiles per unit", K);
+            CHECK(!is(t, true, K, 262145) && !is(t, true, K, 300000) && !is(t, true, K, 393216), "tree K=%d", K);
+            CHECK(is(t, false, K, 262144), "linear K=%d, 4 tiles per unit", K);
+            CHECK(is(t, false, K, 300000) == (t == FC_F32), "linear K=%d, 4.6 tiles per unit", K);
+            CHECK(!is(t, false, K, 393216), "linear K=%d, 6 tiles per unit", K);
+        }
+    CHECK(is(FC_F16, true, 128, 163696) && is(FC_F32, false, 1000, 10304), "short plans of many workers");
+    CHECK(!is(FC_F32, true, 16, 4096) && !is(FC_F32, true, 32, 131072) && is(FC_F32, true, 32, 130000), "K <= 32");
+}
+
 int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}};
+    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();
