@@ -244,8 +244,11 @@ int fc_step(fc_plan* plan, const void* const* grads, float* w, float* v, float l
 
 /* For callers that cannot allocate device memory -- code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation: fc_step in
- * the plan's own schedule, where a TWO_PASS plan of two launches holds the
- * raw sum between them in a fixed device array of FC_NOALLOC_MAX_ELEMS floats
+ * the plan's own schedule, or in two passes where those are faster (a FUSED
+ * plan that was asked for with more than 256 bytes of replicas per parameter, a
+ * RESIDENT fp32 plan of 8 replicas and more with at most one tile per block);
+ * these and TWO_PASS plans of two launches hold the raw sum between the passes in
+ * a fixed device array of FC_NOALLOC_MAX_ELEMS floats
  * (64 MiB) that the library reserves on each GPU it runs on and keeps until
  * the process ends (the other schedules keep the sum on chip).  Arguments,
  * validation and result bits are fc_step's.  When `out` is given it holds the
@@ -254,7 +257,7 @@ int fc_step(fc_plan* plan, const void* const* grads, float* w, float* v, float l
  * FC_NOALLOC_MAX_ELEMS, whatever the schedule (FC_ESIZE).  The current device
  * must be the plan's (FC_EINVAL).  The call allocates no device or host
  * memory and records no per-kernel timing; like every call it replaces a
- * pointer table only when the pointers change.  Calls of TWO_PASS plans on
+ * pointer table only when the pointers change.  Calls in two passes on
  * one GPU use that GPU's one array: those that may run at the same time on
  * one GPU (other plans, other streams or threads) race on it; calls on one
  * plan are ordered (see the conventions above).  The array needs no clearing:

@@ -857,8 +857,8 @@ int update_step_tables(fc_plan* p, const void* const* grads, float* const* bcast
 
 // Two passes on the plan's tiles: the reduce kernel stores the raw sum into
 // `sum`, then the SGD kernel updates w, v from it (and stores the broadcast
-// copies).
-int two_pass(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, float wd, float c, bool bcast,
+// copies).  `sh` is the launch shape of both passes.
+int two_pass(fc_plan* p, const fc::Shape& sh, float* sum, float* w, float* v, float lr, float mu, float wd, float c, bool bcast,
              hipStream_t s, bool timed) {
     fc::ReduceArgs r{};
     r.tiles = p->d_tiles;
@@ -881,8 +881,8 @@ int two_pass(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, flo
     g.wd = wd;
     g.c = c;
     const int rc = launch(p, FC_KERNEL_REDUCE, s, timed,
-                          [&] { return launch_reduce(p->shape, fc::MODE_REDUCE, p->grid, r, s); });
-    return rc ? rc : launch(p, FC_KERNEL_SGD, s, timed, [&] { return fc::launch_sgd(p->shape, p->grid, g, s); });
+                          [&] { return launch_reduce(sh, fc::MODE_REDUCE, p->grid, r, s); });
+    return rc ? rc : launch(p, FC_KERNEL_SGD, s, timed, [&] { return fc::launch_sgd(sh, p->grid, g, s); });
 }
 
 // A step in the plan's schedule, its pointer tables in place; `sum` is where
@@ -890,7 +890,7 @@ int two_pass(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, flo
 int run_step(fc_plan* p, float* sum, float* w, float* v, float lr, float mu, float wd, int batch, float* out,
              bool bcast, hipStream_t s, bool timed) {
     const float c = 1.0f / static_cast<float>(batch);
-    if (two_launches(p)) return two_pass(p, sum, w, v, lr, mu, wd, c, bcast, s, timed);
+    if (two_launches(p)) return two_pass(p, p->shape, sum, w, v, lr, mu, wd, c, bcast, s, timed);
     fc::ReduceArgs a{};
     a.tiles = p->d_tiles;
     a.ntiles = p->ntiles;
@@ -935,10 +935,10 @@ static int fc_step_body(fc_plan* p, const void* const* grads, float* w, float* v
 // fc_step where a plan of two passes keeps the raw sum in the library's fixed
 // device array (fc_update.hip) instead of its own scratch; nothing is
 // allocated, on the device or on the host.  The other schedules keep the sum
-// on chip and run as they are: a reduce and an update pass in their place
-// read and wrote the sum once more and, on the resident plans' one-wave
-// tiles, reduced more slowly (measured on MI355X, us per call: 734016 x K=32
-// fp32 21.2 in two passes, 18.2 resident).
+// on chip and run as they are, except where two passes are the faster
+// (fc::noalloc_two_pass): reading and writing the sum once more costs the
+// others (measured on MI355X, us per call: 734016 x K=32 fp32 21.2 in two
+// passes, 18.2 resident).
 static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, float* v, float lr, float mu,
                                 float wd, int batch, float* out, float* const* bcast_dst, void* stream) {
     int rc = check_step(p, grads, w, v, batch, out, bcast_dst);
@@ -949,7 +949,8 @@ static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, 
     if (dev != p->device) return FC_EINVAL;
     if (p->ntiles == 0) return FC_OK;
     float* sum = out;
-    if (!sum && two_launches(p)) {
+    const bool two = fc::noalloc_two_pass(p->schedule, p->shape.lane != 0, p->K, p->sg, p->ntiles, p->res_grid);
+    if (!sum && two) {
         rc = hip_rc(fc::noalloc_scratch(dev, &sum));
         if (rc) return rc;
     }
@@ -958,7 +959,19 @@ static int fc_step_noalloc_body(fc_plan* p, const void* const* grads, float* w, 
     rc = order_after_last(p, s, note);
     if (rc) return rc;
     rc = update_step_tables(p, grads, bcast_dst, s);
-    if (rc == FC_OK) rc = run_step(p, sum, w, v, lr, mu, wd, batch, out, bcast_dst != nullptr, s, false);
+    if (rc == FC_OK && two) {
+        // a resident plan's batch of 4 replicas has no reduce-kernel instance:
+        // its reduce pass loads batches of 8 (the association does not depend
+        // on the batch)
+        fc::Shape sh = p->shape;
+        if (!fc::compiled_pair(sh.vecs, sh.kchunk)) {
+            sh.kchunk = 8;
+            sh.maxd = bit_length(p->K / sh.kchunk);
+        }
+        rc = two_pass(p, sh, sum, w, v, lr, mu, wd, 1.0f / static_cast<float>(batch), bcast_dst != nullptr, s, false);
+    } else if (rc == FC_OK) {
+        rc = run_step(p, sum, w, v, lr, mu, wd, batch, out, bcast_dst != nullptr, s, false);
+    }
     if (note) note_stream(p, s);
     return rc;
 }

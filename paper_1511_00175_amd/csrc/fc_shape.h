@@ -310,4 +310,18 @@ inline int default_schedule(int K, int bytes_per_element) {
     return static_cast<int64_t>(K) * bytes_per_element > 256 ? FC_SCHED_TWO_PASS : FC_SCHED_FUSED;
 }
 
+// fc_step_noalloc in two passes with the raw sum in the library's fixed array:
+// TWO_PASS plans of two launches, and where a schedule that the caller chose
+// keeps the sum on chip more slowly than that: FUSED with more than 256 bytes
+// of replicas per parameter, and RESIDENT fp32 plans of 8 replicas and more with
+// at most one tile per block.  Measured on MI355X, us, on chip / two passes: FUSED
+// fp16 4 10^6 x K=1000 1660 / 1229, fp32 1.4 10^7 x K=128 1223 / 1139; RESIDENT
+// 65536 x K=16 7.5 / 6.4, 4000 x K=1000 65 / 58 (fp16 65.6 / 65.1, and 400000 x K=8
+// 8.1 / 9.9).
+inline bool noalloc_two_pass(int schedule, bool split, int K, int bytes_per_element, int ntiles, int blocks) {
+    if (split) return false;
+    if (schedule == FC_SCHED_RESIDENT) return bytes_per_element == 4 && K >= 8 && ntiles <= blocks;
+    return schedule == FC_SCHED_TWO_PASS || default_schedule(K, bytes_per_element) == FC_SCHED_TWO_PASS;
+}
+
 }  // namespace fc

@@ -123,11 +123,25 @@ static void split_plans() {
     CHECK(!is(FC_F32, true, 16, 4096) && !is(FC_F32, true, 32, 131072) && is(FC_F32, true, 32, 130000), "K <= 32");
 }
 
+// allocation-free steps that run in two passes
+static void noalloc() {
+    for (int K = 1; K <= 1024; ++K)
+        for (int bytes : {2, 4}) {
+            CHECK(fc::noalloc_two_pass(FC_SCHED_FUSED, false, K, bytes, 100, 0) == (K * bytes > 256), "fused K=%d", K);
+            CHECK(fc::noalloc_two_pass(FC_SCHED_TWO_PASS, false, K, bytes, 100, 0), "two passes K=%d", K);
+            CHECK(!fc::noalloc_two_pass(FC_SCHED_TWO_PASS, true, K, bytes, 100, 0), "passes joined K=%d", K);
+            CHECK(!fc::noalloc_two_pass(FC_SCHED_FUSED, true, K, bytes, 100, 0), "split K=%d", K);
+            CHECK(!fc::noalloc_two_pass(FC_SCHED_RESIDENT, false, K, bytes, 257, 256), "resident K=%d", K);
+            CHECK(fc::noalloc_two_pass(FC_SCHED_RESIDENT, false, K, bytes, 256, 256) == (bytes == 4 && K >= 8),
+                  "resident, one tile a block, K=%d", K);
+        }
+}
+
 int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}};
+    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}, {"noalloc", noalloc}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();

@@ -1,6 +1,7 @@
-"""fc_step_noalloc runs the plan's own schedule: each one (the two-pass plan
-keeps its raw sum in the library's fixed array, the others on chip) against
-fc_step and the oracle, bit for bit, two calls in a row, the second smaller,
+"""fc_step_noalloc runs the plan's own schedule (the two-pass plan keeps its raw
+sum in the library's fixed array, the others on chip), or two passes where those
+are faster (fused with many replicas, resident with one tile per block): each
+against fc_step and the oracle, bit for bit, two calls in a row, the second smaller,
 with and without a buffer for the raw sum."""
 import numpy as np
 import pytest
@@ -20,7 +21,8 @@ def fc(device):
 @pytest.mark.parametrize("K,dtype,order,opts", [
     (20, "f32", "tree", dict(schedule=1)), (20, "f32", "linear", dict(schedule=2)), (70, "f16", "tree", dict(schedule=2)),
     (20, "f32", "tree", dict(schedule=3)), (9, "f16", "linear", dict(schedule=4, max_blocks=2)),
-    (70, "f32", "tree", None), (40, "f16", "linear", None)])
+    (70, "f32", "tree", None), (40, "f16", "linear", None), (70, "f32", "tree", dict(schedule=1)),
+    (16, "f32", "tree", dict(schedule=3)), (130, "f32", "linear", dict(schedule=3))])
 def test_every_schedule(fc, K, dtype, order, opts, with_out):
     rng = np.random.default_rng(K)
     for n in (90_000, 20_000):
