@@ -310,6 +310,13 @@ inline int default_schedule(int K, int bytes_per_element) {
     return static_cast<int64_t>(K) * bytes_per_element > 256 ? FC_SCHED_TWO_PASS : FC_SCHED_FUSED;
 }
 
+// fc_sgd_step on tiles of 64 lanes x 2 vectors (resident plans of few fp32
+// replicas): one thread per vector, two waves per tile.  One wave took a tile's
+// two vectors one after the other, and plans that became resident for their
+// steps lost 5% here.  Measured on MI355X, us, one wave / two: 3.4 10^7
+// parameters 115.9 / 110.7 (64-lane tiles of one vector 108.7), 1.4 10^8 467 / 440.
+inline bool sgd_vector_per_thread(const Shape& sh) { return sh.vecs == 2 && sh.block == 64; }
+
 // fc_step_noalloc in two passes with the raw sum in the library's fixed array:
 // TWO_PASS plans of two launches, and where a schedule that the caller chose
 // keeps the sum on chip more slowly than that: FUSED with more than 256 bytes

@@ -4,6 +4,7 @@
 #include <mutex>
 
 #include "fc_device.h"
+#include "fc_shape.h"
 
 namespace fc {
 
@@ -43,6 +44,10 @@ hipError_t launch_sgd(const Shape& sh, int grid, const SgdArgs& a, hipStream_t s
         hipLaunchKernelGGL((sgd_kernel<4, u.value>), dim3(grid), dim3(sh.block), 0, s, a);
         return hipGetLastError();
     };
+    if (sgd_vector_per_thread(sh)) {
+        hipLaunchKernelGGL((sgd_kernel<4, 1>), dim3(grid), dim3(sh.block * sh.vecs), 0, s, a);
+        return hipGetLastError();
+    }
     if (sh.vecs == 4) return go(I<4>{});
     return pick<1, 2>(sh.vecs, go);
 }

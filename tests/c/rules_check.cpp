@@ -137,11 +137,19 @@ static void noalloc() {
         }
 }
 
+// update-only launches with a thread per vector
+static void sgd() {
+    CHECK(fc::sgd_vector_per_thread(shape(64, 2)), "resident tiles of two vectors");
+    for (int block : {64, 128, 256})
+        for (int vecs : {1, 2, 4})
+            CHECK(fc::sgd_vector_per_thread(shape(block, vecs)) == (block == 64 && vecs == 2), "(%d, %d)", vecs, block);
+}
+
 int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}, {"noalloc", noalloc}};
+    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}, {"noalloc", noalloc}, {"sgd", sgd}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();
