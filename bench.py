@@ -752,7 +752,8 @@ def main():
     prof_us = read_profile_us(variant, dom) if plain else None
     sched = {1: "fused", 2: "two-pass", 3: "resident", 4: "resident, one launch"}.get(info.schedule,
                                                                                       str(info.schedule))
-    rk = "resident_kernel" if resident else "reduce_kernel"
+    rk = ("split_kernel" if info.k_waves > 1 else
+          "resident_kernel" if resident and info.block_threads > 64 else "reduce_kernel")
 
     res = {
         "metric": METRIC,

@@ -327,15 +327,20 @@ typedef struct {
     uint64_t n_elems;    /* sum of segment lengths */
     uint64_t extent;     /* one past the last segment element */
     int ntiles;          /* blocks of work in one launch */
-    int grid;            /* blocks launched (RESIDENT: its persistent grid) */
+    int grid;            /* blocks of the reduce or step launch (RESIDENT: its persistent
+                            grid, or one per tile where it reduces and steps in one pass) */
     int block_threads;   /* threads per block of the reduce or step launch */
     int vecs_per_thread; /* (1 where a lane's share is less than one vector) */
     int kchunk;
     int schedule;        /* resolved fc_schedule of fc_step: FUSED, TWO_PASS, RESIDENT or
-                            RESIDENT_ONE_LAUNCH (only when asked for) */
+                            RESIDENT_ONE_LAUNCH (only when asked for).  TWO_PASS with
+                            k_waves > 1 joins its passes: fc_step is one launch, timed as
+                            FC_KERNEL_STEP */
     uint64_t scratch_bytes; /* device memory the plan owns besides its tables */
-    int k_waves;         /* always 1: one wave reduces all K replicas of a lane-vector */
-    int lds_bytes;       /* RESIDENT: LDS per block (0 for the other schedules) */
+    int k_waves;         /* waves that share the replicas of a tile; 1: one wave reduces all K
+                            replicas of a lane-vector */
+    int lds_bytes;       /* LDS per block of RESIDENT launches and of those whose waves share
+                            the replicas (0 for the others) */
     int rounds;          /* RESIDENT: rounds of the persistent grid (0 otherwise) */
 } fc_plan_info;
 

@@ -602,10 +602,12 @@ int fc_plan_query(const fc_plan* p, fc_plan_info* info) {
     info->kchunk = p->shape.kchunk;
     info->schedule = p->res_one_launch ? FC_SCHED_RESIDENT_ONE_LAUNCH : p->schedule;
     info->scratch_bytes = p->d_sum ? p->extent * sizeof(float) : 0;
-    info->k_waves = 1;
-    info->lds_bytes = p->schedule == FC_SCHED_RESIDENT ? p->res_lds : 0;
+    info->k_waves = p->shape.lane ? p->shape.waves : 1;
+    info->lds_bytes = p->schedule == FC_SCHED_RESIDENT ? p->res_lds
+                      : p->shape.lane                  ? static_cast<int>(fc::split_lds(p->shape))
+                                                       : 0;
     info->rounds = p->schedule == FC_SCHED_RESIDENT ? p->res_rounds : 0;
-    if (p->schedule == FC_SCHED_RESIDENT) {
+    if (p->schedule == FC_SCHED_RESIDENT && !p->res_one_pass) {
         // the launch of fc_step and fc_tree_reduce: one block of 16 waves per compute unit
         info->grid = p->res_grid;
         info->block_threads = 64 * fc::RESIDENT_WAVES;

@@ -79,6 +79,15 @@ constexpr int RESIDENT_CLOCK_WORDS = 4;
 constexpr int RESIDENT_SLOT = 256;  // floats per tile of 64 lanes x one 4-element vector
 constexpr int RESIDENT_WAVES = 16;
 constexpr int SPLIT_WAVES = 16;     // most waves that share a tile (split_kernel)
+constexpr int SPLIT_C = 16;         // replicas per batch of the split and chain kernels
+
+// Dynamic LDS of a reduce or step launch of the split kernel (a row of sums per
+// wave in tree order, of a batch's values in linear order) or the chain kernel
+// (two buffers of a batch per loading wave).
+inline size_t split_lds(const Shape& sh) {
+    if (sh.chain) return sizeof(float) * 64 * 2 * SPLIT_C * (sh.waves - 1);
+    return sizeof(float) * 64 * sh.lane * sh.waves * (sh.tree ? 1 : SPLIT_C);
+}
 
 struct SgdArgs {
     const Tile* tiles;

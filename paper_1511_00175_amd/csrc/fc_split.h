@@ -57,7 +57,6 @@ template <> struct Rep<FC_F16, 2> {
     }
 };
 
-constexpr int SPLIT_C = 16;     // replicas per batch
 constexpr int SPLIT_MAXD = 3;   // pending-subtree stack: runs of up to 4 batches
 
 // The wave's vector of replicas [k, k + n), n <= SPLIT_C (nothing for n <= 0).
@@ -342,10 +341,6 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void chain_kernel(ReduceArgs a) {
     }
 }
 
-inline size_t chain_lds(const Shape& sh) {
-    return sizeof(float) * 64 * 2 * SPLIT_C * (sh.waves - 1);
-}
-
 // Allow the chain kernel `lds` bytes of dynamic LDS (a property of the kernel,
 // set when a plan that runs it is created).
 template <int DT> hipError_t prepare_chain_dt(size_t lds) {
@@ -362,13 +357,12 @@ template <int DT>
 hipError_t launch_split_dt(const Shape& sh, int mode, int grid, const ReduceArgs& a, hipStream_t s) {
     if (sh.chain) {
         return pick<MODE_REDUCE, MODE_STEP>(mode, [&](auto md) {
-            hipLaunchKernelGGL((chain_kernel<DT, md.value>), dim3(grid), dim3(64 * sh.waves), chain_lds(sh), s, a);
+            hipLaunchKernelGGL((chain_kernel<DT, md.value>), dim3(grid), dim3(64 * sh.waves), split_lds(sh), s, a);
             return hipGetLastError();
         });
     }
-    const size_t lds = sizeof(float) * 64 * sh.lane * sh.waves * (sh.tree ? 1 : SPLIT_C);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * sh.waves), lds, s, a, sh.run);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * sh.waves), split_lds(sh), s, a, sh.run);
         return hipGetLastError();
     };
     return pick<MODE_REDUCE, MODE_STEP>(mode, [&](auto md) {

@@ -32,7 +32,10 @@ def test_several_rounds(fc, K, dtype, below, above):
 def test_one_pass_fp16(fc, K, order):
     rows = [(0, 4_194_301, 1.0, 1.0), (4_194_304, 259, 2.0, 0.0), (4_194_564, 3, 1.0, 1.0)]
     p = fc.Plan(rows, K, "f16", order)
-    assert (p.info().schedule, p.info().rounds) == (3, 1)
+    info = p.info()
+    assert (info.schedule, info.rounds) == (3, 1)
+    # reduce and step launch a block per tile, not the persistent grid
+    assert (info.grid, info.block_threads, info.k_waves) == (info.ntiles, 64, 1)
     p.close()
     rng = np.random.default_rng(K)
     bad, _, _ = run_reduce(fc, rows, K, "f16", order, rng, special=True)

@@ -46,6 +46,11 @@ def test_narrow_tiles_match_oracle(fc, K, order, dtype):
     p.close()
     assert (info.ntiles, info.kchunk, info.scratch_bytes) == (tiles(NARROW, 64), 16, 0)
     assert 2 <= info.block_threads // 64 <= 16
+    # what the plan reports is the launch: the waves that share a tile, and their LDS
+    assert info.k_waves == info.block_threads // 64
+    chain = order == "linear" and K >= 640
+    rows = 2 * 16 * (info.k_waves - 1) if chain else info.k_waves * (1 if order == "tree" else 16)
+    assert info.lds_bytes == rows * 64 * 4
     rng = np.random.default_rng(K)
     bad, _, _ = run_reduce(fc, NARROW, K, dtype, order, rng, special=True)
     assert bad == 0
