@@ -1,12 +1,14 @@
 """Default plans above 64 MiB: large plans of several rounds are resident from
 32 bytes of replicas per parameter on, and a one-round plan of few fp16
 replicas runs its calls in one pass over the resident tiles, except a step
-that broadcasts to more than 4 copies; every call against the oracle, bit for
-bit, on a ragged table."""
+that broadcasts to more than 4 copies.  Reduce and step against the oracle, bit
+for bit: the large plans on windows at the table's ends, its tails and the
+borders of their rounds, the others on every element of a ragged table."""
 import numpy as np
 import pytest
 
-from gpu_cases import run_reduce, run_steps
+from gpu_cases import LR, MU, WD, run_reduce, run_steps, same_bits
+import oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -25,6 +27,42 @@ def test_several_rounds(fc, K, dtype, below, above):
         assert p.info().schedule == sched
         assert p.info().rounds >= 2 or sched == 1
         p.close()
+
+
+@pytest.mark.parametrize("K,dtype", [(8, "f32"), (16, "f16")])
+def test_several_rounds_match_oracle(fc, K, dtype):
+    import torch
+    n = (1 << 25) + 4099
+    rows = [(0, n - 70_000, 1.0, 1.0), ((n - 70_000 + 3) // 4 * 4, 70_001, 2.0, 0.0)]
+    ext = rows[1][0] + rows[1][1]
+    p = fc.Plan(rows, K, dtype, "tree")
+    info = p.info()
+    assert (info.schedule, info.rounds) == (3, 2 if dtype == "f32" else 3)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    reps = torch.empty((K, (ext + 63) // 64 * 64), dtype=getattr(torch, {"f32": "float32", "f16": "float16"}[dtype]),
+                       device="cuda").normal_(0, 0.01, generator=g)
+    w = torch.empty(ext, device="cuda").normal_(0, 0.05, generator=g)
+    v = torch.empty(ext, device="cuda").normal_(0, 1e-3, generator=g)
+    w0, v0, out = w.clone(), v.clone(), torch.full((ext,), -1.0, device="cuda")
+    p.tree_reduce(reps, out)
+    p.step(reps, w, v, LR, MU, WD, 256)
+    torch.cuda.synchronize()
+    p.close()
+    # windows of 2^17 elements at both ends and around every round's first tile
+    tile = info.vecs_per_thread * 256
+    starts = [0, rows[1][0] - 4096 * 8] + [-(-info.ntiles * r // info.rounds) * tile // 4 * 4 - (1 << 16)
+                                           for r in range(1, info.rounds)]
+    for a in starts:
+        b = min(a + (1 << 17), ext)
+        segs = [(max(o, a) - a, min(o + m, b) - max(o, a), x, y) for o, m, x, y in rows if o < b and o + m > a]
+        win = [r[a:b].cpu().numpy() for r in reps]
+        ew, ev, _, _ = oracle.step(segs, win, w0[a:b].cpu().numpy(), v0[a:b].cpu().numpy(), LR, MU, WD, 256)
+        eo = oracle.tree_reduce(segs, win, out=np.full(b - a, -1.0, np.float32))
+        assert same_bits(w[a:b].cpu().numpy(), ew) == 0 and same_bits(v[a:b].cpu().numpy(), ev) == 0, a
+        assert same_bits(out[a:b].cpu().numpy(), eo) == 0, a
+    del reps, w, v, w0, v0, out
+    torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("order", ["tree", "linear"])

@@ -80,10 +80,11 @@ def test_special_values(fc, K, order, dtype):
 
 @pytest.mark.parametrize("K", [256, 1000, 1024])
 def test_many_workers(fc, K):
-    """K beyond 31 chunks uses the deeper pending-subtree stack, in the
-    default schedule and in the resident kernel (its depth-7 instances)."""
+    """K beyond 31 chunks uses the deeper pending-subtree stack, in the fused
+    and two-pass kernels and in the resident kernel (its depth-7 instances);
+    the default plan's waves share the replicas."""
     segs = [(0, 1000, 1, 1), (1024, 37, 1, 1), (1088, 8, 1, 1)]
-    for opts in (None, dict(schedule=3)):
+    for opts in (None, dict(schedule=1), dict(schedule=2), dict(schedule=3)):
         for dtype in ("f32", "f16"):
             for order in ("tree", "linear"):
                 bad, _, _ = run_reduce(fc, segs, K, dtype, order, np.random.default_rng(K), opts=opts)
@@ -193,8 +194,9 @@ def test_schedules_match_oracle(fc, K, schedule, order, dtype):
 
 
 def test_schedule_resolution(fc):
-    """AUTO keeps steps of less than 64 MiB on the fused kernel (two passes
-    when a parameter's replicas exceed 256 bytes); above that it takes the
+    """AUTO keeps steps of less than 64 MiB off the resident kernel (FUSED, or
+    TWO_PASS when a parameter's replicas exceed 256 bytes, whose passes short
+    plans of many workers join in one launch); above that it takes the
     resident schedule when every block's share of tiles fits a compute
     unit's LDS; otherwise two passes when a parameter's replicas exceed 256
     bytes, only then with a raw-sum scratch buffer."""

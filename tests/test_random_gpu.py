@@ -96,8 +96,8 @@ def test_random_composed_step_matches_oracle(fc, seed):
 
 @pytest.mark.parametrize("seed", range(2000, 2032))
 def test_random_step_noalloc_matches_oracle(fc, seed):
-    """fc_step_noalloc (the step in two passes with the raw sum in the
-    library's fixed device array) on seeded random configurations, two
+    """fc_step_noalloc (the plan's own schedule, or two passes with the raw sum
+    in the library's fixed device array) on seeded random configurations, two
     chained steps of shrinking size: w', v' and the optional outputs equal
     the oracle's."""
     import torch

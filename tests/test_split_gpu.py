@@ -3,11 +3,12 @@ which short plans of more than 16 workers run, against the oracle bit for bit:
 worker counts at the edges of its batches (16), runs (16, 32, 64) and waves
 (16), tile widths of 64 and 128 elements with lengths around them, tails, both
 orders and storage types, a cap on the grid that its tiles do not reach, special
-values, every optional output, and the raw sum written over a replica."""
+values, every optional output, and the raw sum written over a replica; for the
+chain kernel too, where one wave adds what the others load."""
 import numpy as np
 import pytest
 
-from gpu_cases import alloc_len, host_replicas, run_reduce, run_steps, same_bits, to_dev
+from gpu_cases import LR, MU, WD, alloc_len, host_replicas, run_reduce, run_steps, same_bits, to_dev
 import oracle
 
 pytestmark = pytest.mark.gpu
@@ -71,6 +72,45 @@ def test_wide_tiles_match_oracle(fc, K, max_blocks, order, dtype):
     bad, _, _ = run_reduce(fc, WIDE, K, dtype, order, rng, opts=opts, special=True)
     assert bad == 0
     assert run_steps(fc, WIDE, K, dtype, order, rng, steps=2, opts=opts, with_out=True, with_bcast=K < 150) == 0
+
+
+# few enough tiles for the chain kernel (linear order, at most one tile of 64
+# elements per compute unit), with tails of one to three elements
+CHAIN = rows_of([2000, 1, 65, 64, 3, 130, 4, 62, 259])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("K", [640, 655, 1000, 1024])
+def test_chain_with_every_output(fc, K, dtype):
+    """One wave adds, the others load into two buffers in turn; w' goes through
+    one of them to the waves that share the copies."""
+    p = fc.Plan(CHAIN, K, dtype, "linear")
+    info = p.info()
+    p.close()
+    assert (info.ntiles, info.k_waves, info.lds_bytes) == (tiles(CHAIN, 64), 16, 2 * 15 * 16 * 64 * 4)
+    rng = np.random.default_rng(K)
+    assert run_steps(fc, CHAIN, K, dtype, "linear", rng, steps=2, with_out=True, with_bcast=True) == 0
+    assert run_steps(fc, CHAIN, K, dtype, "linear", rng, steps=1, special=True) == 0
+
+
+@pytest.mark.parametrize("order,K", [("tree", 70), ("linear", 70), ("linear", 700)])
+def test_step_with_its_sum_over_a_replica(fc, order, K):
+    import torch
+    n = alloc_len(CHAIN)
+    rng = np.random.default_rng(K)
+    reps = host_replicas(rng, K, n, np.float32, scale=0.01)
+    w = rng.standard_normal(n, dtype=np.float32)
+    v = rng.standard_normal(n, dtype=np.float32) * np.float32(1e-3)
+    for k in (0, 15, 16, K - 1):
+        out = reps[k].copy()
+        ew, ev, _, _ = oracle.step(CHAIN, list(reps), w, v, LR, MU, WD, 256, order=order, out=out)
+        d, wd, vd = to_dev(reps), to_dev(w), to_dev(v)
+        plan = fc.Plan(CHAIN, K, "f32", order)
+        plan.step(d, wd, vd, LR, MU, WD, 256, out=d[k])
+        torch.cuda.synchronize()
+        plan.close()
+        assert same_bits(wd.cpu().numpy(), ew) == 0 and same_bits(vd.cpu().numpy(), ev) == 0, k
+        assert same_bits(d[k].cpu().numpy(), out) == 0, k
 
 
 @pytest.mark.parametrize("order", ["tree", "linear"])

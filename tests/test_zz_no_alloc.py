@@ -1,10 +1,11 @@
-"""fc_step_noalloc (the step with its raw sum in the library's fixed device
+"""fc_step_noalloc (a two-pass step keeps its raw sum in the library's fixed device
 array) against fc_step on the same plan and inputs, bit for bit, through the
 C ABI: two calls in a row, the second on a smaller plan, so that the array
 still holds the first call's sums when the second runs.  Also the size limit
 (FC_ESIZE, refused before anything is enqueued), an `out` buffer (the array
-unused), the broadcast, fp16 replicas, the linear order and a resident plan
-whose tiles the reduce pass reads in batches of 8."""
+unused), the broadcast, fp16 replicas, the linear order, plans of the other
+schedules and a resident plan that takes two passes on its tiles of two vectors,
+which the reduce pass reads in batches of 8."""
 import numpy as np
 import pytest
 
@@ -75,7 +76,8 @@ def big_table(rng, n_total, dtype):
 
 
 @pytest.mark.parametrize("dtype,order,K,opts", [
-    ("f32", "tree", 70, None),              # a two-pass plan: fc_step uses the plan's own scratch
+    ("f32", "tree", 70, dict(schedule=2)),  # a two-pass plan: fc_step uses the plan's own scratch
+    ("f32", "tree", 70, None),              # resident, then the waves share the replicas
     ("f32", "tree", 9, None),               # a fused plan (no scratch of its own)
     ("f16", "linear", 33, None),
     ("f32", "tree", 16, dict(schedule=3)),  # resident tiles of 2 vectors, batches of 4
@@ -95,9 +97,12 @@ def test_noalloc_equals_step_twice(fc, dtype, order, K, opts):
 @pytest.mark.parametrize("with_out,with_bcast", [(True, False), (False, True), (True, True)])
 def test_noalloc_with_sum_and_broadcast(fc, with_out, with_bcast):
     rng = np.random.default_rng(3)
-    for segs, K in ((big_table(rng, 400_000, "f32"), 12), (big_table(rng, 100_000, "f32"), 5)):
-        vs_step, vs_oracle = run_both(fc, segs, K, "f32", "tree", rng, with_out=with_out, with_bcast=with_bcast)
-        assert vs_step == 0 and vs_oracle == 0, (K, vs_step, vs_oracle)
+    for segs, K, opts in ((big_table(rng, 400_000, "f32"), 12, None), (big_table(rng, 100_000, "f32"), 5, None),
+                          (big_table(rng, 400_000, "f32"), 12, dict(schedule=2)),
+                          (big_table(rng, 100_000, "f32"), 12, dict(schedule=3))):
+        vs_step, vs_oracle = run_both(fc, segs, K, "f32", "tree", rng, opts=opts, with_out=with_out,
+                                      with_bcast=with_bcast)
+        assert vs_step == 0 and vs_oracle == 0, (K, opts, vs_step, vs_oracle)
 
 
 def test_noalloc_size_limit(fc):
