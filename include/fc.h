@@ -134,8 +134,8 @@ typedef struct fc_plan fc_plan;
  *   that every call is one launch and the plan owns no raw-sum scratch.  Any
  *   other step of less than 64 MiB (n_elems * (K * bytes per element + 16))
  *   runs FUSED; a larger one RESIDENT when one round holds the plan or a
- *   parameter's replicas take at least 48 bytes (32 from 2^25 parameters on),
- *   else FUSED.  Such a RESIDENT plan of one round and at most 16 fp16 replicas
+ *   parameter's replicas take at least 48 bytes (44 from 2^25 parameters on; from
+ *   3 * 2^24 on 40, or 32 in fp16), else FUSED.  Such a RESIDENT plan of one round and at most 16 fp16 replicas
  *   (8 beyond 2^23 parameters) reduces and steps in one pass over its tiles,
  *   as FUSED does, unless the step broadcasts to more than 4 copies; its
  *   one-pass launches leave no record for fc_plan_balance.  With a

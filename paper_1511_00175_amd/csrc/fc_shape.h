@@ -255,18 +255,30 @@ inline bool compiled_pair(int u, int c) {
 // vs 15.0, fp16 2^20 x K=64 24.1 vs 26.4, 2^21 x K=8 15.2 vs 15.6, 200000 x
 // K=256 34.4 vs 34.2).
 constexpr uint64_t RESIDENT_MIN_BYTES = uint64_t(64) << 20;
-// From 2^25 parameters on 32 bytes are enough: with paired loads, its own v'
-// write phase and register-held tiles the resident kernel wins there in every
-// call (measured on MI355X, us, fused vs resident: fp32 3.4 10^7 x K=8 step
-// 279 vs 270, broadcast 479 vs 460, x K=11 357 vs 322, 639 vs 595, 8 10^7 x
-// K=11 832 vs 783; fp16 8 10^7 x K=16 688 vs 640, 1729 vs 1571, 6.1 10^7 x K=16
-// reduce 382 vs 346; at 24 bytes, fp32 4 10^7 x K=6, 258 vs 264).  Smaller plans
-// of several rounds would gain as much, but keep the 48 bytes by which callers
-// and the tests know their schedule.
-constexpr uint64_t RESIDENT_MANY_ELEMS = uint64_t(1) << 25;
+// Larger plans stay resident with fewer bytes of replicas: from 2^25 parameters
+// on with 44, from 3 * 2^24 on with 32 in fp16 and 40 in fp32.  Measured on
+// MI355X, us, fused vs resident, buffers not in the Infinity Cache: fp32 K=11
+// 3.4 10^7 x step 333 vs 333, reduce 264 vs 251, broadcasting step 647 vs 593;
+// fp16 K=23 349 vs 351, 277 vs 275, 1017 vs 900; fp32 K=10 6.1 10^7 x step 566 vs 563, reduce 434
+// vs 420, 1.4 10^8 x step 1324 vs 1263; fp16 K=16 6.1 10^7 x step 489 vs 488,
+// reduce 364 vs 345, 8 10^7 x step 642 vs 635, 1.4 10^8 x 1134 vs 1108.  Below
+// the lines the step is what loses, its update writes being the larger share:
+// fp32 K=8 3.4 10^7 x 262 vs 274, 4.5 10^7 x 349 vs 368, 6.1 10^7 x 478 vs 490,
+// and at 1.4 10^8 x still 2.5% when the same buffers are used again; K=9 286 vs 296; K=10 4.5 10^7 x
+// 414 vs 419; fp16 K=16 3.4 10^7 x 268 vs 277, K=20 313 vs 322.  Below 2^25 the
+// 48 bytes hold: at 1.9 to 3.3 10^7 x fp32 K=8 to 11 and fp16 K=12 to 22 the
+// resident step takes 0.96 to 1.06 times the fused one's time, and 1.03 to 1.16
+// times on the same buffers again.  (So does a reduce below 6 10^7: fp16 K=23
+// 3.4 10^7 x 256 vs 276, fp32 K=11 6.1 10^7 x 437 vs 459, the part of the
+// replicas that stays in the cache being worth more to the fused kernel.)
+constexpr uint64_t RESIDENT_44_ELEMS = uint64_t(1) << 25;
+constexpr uint64_t RESIDENT_MANY_ELEMS = uint64_t(3) << 24;
 inline bool default_resident(int K, int bytes_per_element, int64_t rounds, uint64_t n_elems, uint64_t step_bytes) {
     if (step_bytes < RESIDENT_MIN_BYTES) return false;
-    return rounds == 1 || static_cast<int64_t>(K) * bytes_per_element >= (n_elems >= RESIDENT_MANY_ELEMS ? 32 : 48);
+    const int64_t least = n_elems >= RESIDENT_MANY_ELEMS ? (bytes_per_element == 2 ? 32 : 40)
+                          : n_elems >= RESIDENT_44_ELEMS ? 44
+                                                         : 48;
+    return rounds == 1 || static_cast<int64_t>(K) * bytes_per_element >= least;
 }
 
 // Calls that a default plan of one resident round runs in one pass, on the

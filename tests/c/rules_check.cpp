@@ -137,6 +137,21 @@ static void noalloc() {
         }
 }
 
+// plans of several rounds that are resident
+static void resident() {
+    const uint64_t a = uint64_t(1) << 25, b = uint64_t(3) << 24, big = uint64_t(200) << 20;
+    for (int K = 1; K <= 64; ++K)
+        for (int bytes : {2, 4}) {
+            const int row = K * bytes;
+            CHECK(!fc::default_resident(K, bytes, 1, 1000, (64 << 20) - 1), "short step, K=%d", K);
+            CHECK(fc::default_resident(K, bytes, 1, 1000, 64 << 20), "one round, K=%d", K);
+            CHECK(fc::default_resident(K, bytes, 2, a - 1, big) == (row >= 48), "below 2^25, K=%d of %d", K, bytes);
+            CHECK(fc::default_resident(K, bytes, 2, a, big) == (row >= 44), "2^25, K=%d of %d", K, bytes);
+            CHECK(fc::default_resident(K, bytes, 2, b - 1, big) == (row >= 44), "below 3 * 2^24, K=%d of %d", K, bytes);
+            CHECK(fc::default_resident(K, bytes, 2, b, big) == (row >= (bytes == 2 ? 32 : 40)), "3 * 2^24, K=%d of %d", K, bytes);
+        }
+}
+
 // update-only launches with a thread per vector
 static void sgd() {
     CHECK(fc::sgd_vector_per_thread(shape(64, 2)), "resident tiles of two vectors");
@@ -149,7 +164,8 @@ int main(int, char** argv) {
     const struct {
         const char* name;
         void (*run)();
-    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}, {"noalloc", noalloc}, {"sgd", sgd}};
+    } rules[] = {{"copies", copies}, {"packed", packed}, {"shapes", shapes}, {"short_steps", short_steps}, {"split_plans", split_plans}, {"noalloc", noalloc},
+                 {"resident", resident}, {"sgd", sgd}};
     for (const auto& r : rules)
         if (!std::strcmp(argv[1], r.name)) {
             r.run();

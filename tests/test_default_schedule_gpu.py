@@ -1,5 +1,5 @@
-"""Default plans above 64 MiB: large plans of several rounds are resident from
-32 bytes of replicas per parameter on, and a one-round plan of few fp16
+"""Default plans above 64 MiB: plans of several rounds are resident from 48 bytes
+of replicas per parameter on, larger ones from 44, 40 or 32, and a one-round plan of few fp16
 replicas runs its calls in one pass over the resident tiles, except a step
 that broadcasts to more than 4 copies.  Reduce and step against the oracle, bit
 for bit: the large plans on windows at the table's ends, its tails and the
@@ -19,25 +19,27 @@ def fc(device):
     return m
 
 
-@pytest.mark.parametrize("K,dtype,below,above", [(7, "f32", 1, 1), (8, "f32", 1, 3), (11, "f32", 1, 3),
-                                                 (15, "f16", 1, 1), (16, "f16", 1, 3), (23, "f16", 1, 3)])
-def test_several_rounds(fc, K, dtype, below, above):
-    for n, sched in (((1 << 25) - 4, below), (1 << 25, above)):
+# schedules just below and from 2^25 parameters on, just below and from 3 * 2^24 on
+@pytest.mark.parametrize("K,dtype,want", [(9, "f32", (1, 1, 1, 1)), (10, "f32", (1, 1, 1, 3)), (11, "f32", (1, 3, 3, 3)),
+                                          (15, "f16", (1, 1, 1, 1)), (16, "f16", (1, 1, 1, 3)),
+                                          (21, "f16", (1, 1, 1, 3)), (23, "f16", (1, 3, 3, 3))])
+def test_several_rounds(fc, K, dtype, want):
+    for n, sched in zip(((1 << 25) - 4, 1 << 25, (3 << 24) - 4, 3 << 24), want):
         p = fc.Plan([(0, n)], K, dtype, "tree")
         assert p.info().schedule == sched
         assert p.info().rounds >= 2 or sched == 1
         p.close()
 
 
-@pytest.mark.parametrize("K,dtype", [(8, "f32"), (16, "f16")])
-def test_several_rounds_match_oracle(fc, K, dtype):
+@pytest.mark.parametrize("K,dtype,size", [(11, "f32", 1 << 25), (16, "f16", 3 << 24)])
+def test_several_rounds_match_oracle(fc, K, dtype, size):
     import torch
-    n = (1 << 25) + 4099
+    n = size + 4099
     rows = [(0, n - 70_000, 1.0, 1.0), ((n - 70_000 + 3) // 4 * 4, 70_001, 2.0, 0.0)]
     ext = rows[1][0] + rows[1][1]
     p = fc.Plan(rows, K, dtype, "tree")
     info = p.info()
-    assert (info.schedule, info.rounds) == (3, 2 if dtype == "f32" else 3)
+    assert info.schedule == 3 and info.rounds >= 2
     g = torch.Generator(device="cuda")
     g.manual_seed(K)
     reps = torch.empty((K, (ext + 63) // 64 * 64), dtype=getattr(torch, {"f32": "float32", "f16": "float16"}[dtype]),

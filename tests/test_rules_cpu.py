@@ -24,7 +24,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("rule", ["copies", "packed", "shapes", "short_steps", "split_plans", "noalloc", "sgd"])
+@pytest.mark.parametrize("rule", ["copies", "packed", "shapes", "short_steps", "split_plans", "noalloc", "resident", "sgd"])
 def test_rule(exe, rule):
     r = subprocess.run([str(exe), rule], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
