@@ -127,16 +127,16 @@ typedef struct fc_plan fc_plan;
  *   so one round's writes meet the next round's replica reads.
  * AUTO (no launch-shape field given): a plan of more than 16 replicas and at
  *   most 4 tiles of 256 elements per compute unit (3 for 400 fp32 replicas and
- *   more; in linear order 5.5, for fp16 replicas 4.5; with K <= 32 fewer than 2) runs FUSED, or TWO_PASS
- *   with both passes in one launch when a parameter's replicas take more than
+ *   more; in linear order 5.5, for fp16 replicas 4.5; with K <= 32 fewer than
+ *   2) runs FUSED, or TWO_PASS with both passes in one launch when a parameter's replicas take more than
  *   256 bytes (K * bytes per element): its waves share the replicas of a
  *   tile, and the sum goes from the reduction to the update through LDS, so
  *   that every call is one launch and the plan owns no raw-sum scratch.  Any
  *   other step of less than 64 MiB (n_elems * (K * bytes per element + 16))
  *   runs FUSED; a larger one RESIDENT when one round holds the plan or a
  *   parameter's replicas take at least 48 bytes (44 from 2^25 parameters on; from
- *   3 * 2^24 on 40, or 32 in fp16), else FUSED.  Such a RESIDENT plan of one round and at most 16 fp16 replicas
- *   (8 beyond 2^23 parameters) reduces and steps in one pass over its tiles,
+ *   3 * 2^24 on 40, or 32 in fp16), else FUSED.  Such a RESIDENT plan of one
+ *   round and at most 16 fp16 replicas (8 beyond 2^23 parameters) reduces and steps in one pass over its tiles,
  *   as FUSED does, unless the step broadcasts to more than 4 copies; its
  *   one-pass launches leave no record for fc_plan_balance.  With a
  *   launch-shape field: TWO_PASS when they take more than 256 bytes, else
@@ -164,8 +164,8 @@ typedef enum {
  * else (1, 16, 64); otherwise (also with an explicit schedule
  * or shape field) fp16 -> (4 vectors, 4 replicas, 256
  * threads); fp32 with K <= 2, or K <= 4 below 2^23 parameters or with max_blocks
- * -> (1, 8, 256); fp32 with 16 < K <= 64 -> (4, 2, 256); other fp32 -> (1, 16, 64).  Replica loads always carry the
- * streaming (nt) hint. */
+ * -> (1, 8, 256); fp32 with 16 < K <= 64 -> (4, 2, 256); other fp32 -> (1, 16, 64).  Replica
+ * loads of two or more elements per lane carry the streaming (nt) hint. */
 typedef struct {
     int block_threads;   /* 64, 128 or 256 threads per block */
     int vecs_per_thread; /* 4-element lane-vectors per thread (1, 2 or 4) ... */

@@ -33,6 +33,8 @@
 //   reduce_kernel   one tile per block; reduce-only, or the fused step
 //   split_kernel    the same for short steps, the replicas of a tile shared by
 //                   the waves of a block (fc_split.h)
+//   chain_kernel    the same in linear order with many replicas and at most one
+//                   tile per CU: one wave adds what the others load (fc_split.h)
 //   resident_kernel one persistent block per CU: reduce a range of tiles into
 //                   LDS and registers (pure reads), then finish it from there:
 //                   w' stored, v' parked and stored after a barrier (or, with

@@ -136,8 +136,9 @@ inline void short_shape(fc_dtype gdt, int K, int cus, uint64_t tiles256, uint64_
 
 // The chain kernel (linear order, at most one tile per unit: wave 0 adds what the
 // others load) from this many replicas on, and the LDS of its two buffers.  A
-// dependent addition takes about 7 ns here, so the serial chain is what is left;
-// with fewer replicas the wave that does not load costs more than it saves.
+// replica costs 5.7 ns on up to 64 tiles, 3.3-3.7 of them the dependent addition
+// with its operand from LDS, and 11 on 256 tiles, where the loads bound it; with
+// fewer replicas the wave that does not load costs more than it saves.
 // Measured on MI355X (us per call in a graph, split / chain): fp32 8274 x K=1000
 // 13.5 / 12.2, 4096 x K=1000 12.1 / 10.3, 16384 x K=1000 14.4 / 13.9, 8000 x K=900
 // with broadcast 16.2 / 14.1, fp16 4096 x K=700 10.2 / 9.3; 4096 x K=512 6.3 / 6.6,

@@ -21,7 +21,7 @@
 // to fp32, and the element's owner adds them in order while the next batches
 // are on their way.
 //
-// The element's owner (thread e of the block, 1 to V elements per thread)
+// The element's owner (thread e of the block owns element e of the tile)
 // loads w and v before the replicas and applies the update; a broadcast takes
 // w' through LDS and spreads the K destinations over the waves.
 #pragma once
@@ -267,13 +267,16 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void split_kernel(ReduceArgs a, i
     else split_tile<DT, 1, TREE, MODE>(a, run, lds, tile.start, tile.count, lr_j, wd_j);
 }
 
-// Linear order where a tile has a compute unit to itself: the additions' serial
-// chain is then all there is, so wave 0 does nothing else.  The other waves put
+// Linear order where a tile has a compute unit to itself: the time goes with the
+// additions' serial chain, so wave 0 does nothing else.  The other waves put
 // batches of SPLIT_C replicas into one of two LDS buffers, one barrier per
 // buffer, while wave 0 adds the other one.  Tiles of 64 elements; element e is
-// lane e of wave 0.  What is left is the additions' latency: 1000 of them take
-// about 7 us (8274 x K=1000 fp32 12.2 us per step, of which 2.5 an empty launch;
-// 13.5 with waves that load and add in turn); two batches per wave on their way
+// lane e of wave 0.  8274 x K=1000 fp32 takes 12.2 us per step, of which 2.5 an
+// empty launch (13.5 with waves that load and add in turn).  A dependent fp32
+// addition alone takes 1.9-2.1 ns, with its operand from LDS in batches of 16
+// 3.3-3.7; from K=640 to 1024 a replica more costs 5.7 ns with 1 or 64 tiles,
+// the rest being the barriers and waits at each buffer, 7.7 with 128 tiles and
+// 11.1 with 256, where the loads bound it.  Two batches per wave on their way
 // instead of one, 32 values read from LDS at a time instead of 16, or one wait
 // for each batch of reads changed nothing.
 template <int DT, int MODE>
