@@ -584,7 +584,9 @@ template <int W, bool PACKED> struct WaveTiles {
 // broadcast copy; a wave of few tiles waits longer for the one load.  Measured
 // on MI355X (us per call, a load per tile / per round, both builds alternated):
 // fp16 6.1 10^7 x K=16 reduce 353.0 / 339.4; a wave of one or two tiles, 2 10^6 x
-// K=2 fp16 reduce 7.1 / 7.5, 4 10^6 x K=2 fp32 reduce 8.3 / 9.6, x K=4 step 21.6 / 23.3.
+// K=2 fp16 reduce 7.1 / 7.5, 4 10^6 x K=2 fp32 reduce 8.3 / 9.6, x K=4 step 21.6 / 23.3;
+// waves of seven, 7.6 10^6 fp32, plain steps 1% slower packed, broadcasting ones
+// 0 to 2% faster (K=32 339.7 / 336.8, K=64 656 / 655, K=128 even).
 // A descriptor is packed into two registers (the kernel has none to spare):
 // 55 bits of start / 4 -- no address reaches further --, 8 of the count (at most
 // 128 vectors) and the tail bit.

@@ -271,8 +271,9 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void split_kernel(ReduceArgs a, i
 // additions' serial chain, so wave 0 does nothing else.  The other waves put
 // batches of SPLIT_C replicas into one of two LDS buffers, one barrier per
 // buffer, while wave 0 adds the other one.  Tiles of 64 elements; element e is
-// lane e of wave 0.  8274 x K=1000 fp32 takes 12.2 us per step, of which 2.5 an
-// empty launch (13.5 with waves that load and add in turn).  A dependent fp32
+// lane e of wave 0.  8274 x K=1000 fp32 takes 10.7 us per step, of which 2.5 an
+// empty launch (12.2 while a block could take several tiles, and then 13.5 with
+// waves that load and add in turn).  A dependent fp32
 // addition alone takes 1.9-2.1 ns, with its operand from LDS in batches of 16
 // 3.3-3.7; from K=640 to 1024 a replica more costs 5.7 ns with 1 or 64 tiles,
 // the rest being the barriers and waits at each buffer, 7.7 with 128 tiles and
